@@ -229,7 +229,9 @@ int64_t saf3r_select_workspace_bytes(const saf3r_problem* problem, const saf3r_h
  * the log of the sum of the bf16-rounded weights exp(z_u - max) plus max: it
  * differs from the fp32 log-sum-exp by up to 2^-8 (bf16's relative rounding
  * of each weight), and a caller that merges lse across launches inherits that
- * bias. fp32 inputs: everything in fp32.
+ * bias. fp32 inputs: to fp32 accuracy throughout (every operand as a scaled
+ * pair of f16 values on the f16 matrix cores, fp32 accumulation, softmax and
+ * row sums in fp32; values outside that form's range on the fp32 ones).
  *   q, k, v      device [heads, N, 64] of problem->dtype
  *   block_idx, block_cnt, cap   as written by saf3r_select_blocks; entries of
  *                DENSE and STRIDE heads are not read. A list that is not
@@ -254,7 +256,9 @@ int64_t saf3r_select_workspace_bytes(const saf3r_problem* problem, const saf3r_h
  *                load balance: list or dense heads whose query blocks walk
  *                at least 32 (bf16) or 8 (fp32) key blocks, more than twice
  *                the key blocks that all list and dense heads' query blocks
- *                walk, divided by 2048 wave slots), and a second launch merges
+ *                walk, divided by 2048 wave slots; an fp32 launch splits of
+ *                these only rows of 64 or more key blocks, more than twice
+ *                that work divided by 512), and a second launch merges
  *                the 4 partial softmax results per query in a fixed order
  *                (results differ from the unsplit launch only by fp32
  *                rounding and the bf16 rounding of P against each range's

@@ -316,6 +316,14 @@ static bool attention_split(const Shape& s, const saf3r_head_cfg* table, int h, 
   return cost >= min_blocks && (int64_t)cost * saf3r::kWaveSlots > 2 * work;
 }
 
+// Which of those heads a launch does split. In bf16 all of them; an fp32 item
+// is four waves already, so only rows of kSplitMinBlocksF32 or more key blocks
+// that outlast twice the layer's work per workgroup slot (kWaveSlots / 4).
+static bool splits_now(const Shape& s, int cost, int64_t work) {
+  return s.dtype == SAF3R_BF16 ||
+         (cost >= saf3r::kSplitMinBlocksF32 && (int64_t)cost * (saf3r::kWaveSlots / 4) > 2 * work);
+}
+
 int64_t saf3r_attention_workspace_bytes(const saf3r_problem* problem, const saf3r_head_cfg* table) {
   Shape s;
   saf3r_status st = check_problem(problem, &s);
@@ -386,7 +394,7 @@ saf3r_status saf3r_sparse_attention(const saf3r_problem* problem, const saf3r_he
     a.dense[h] = p == SAF3R_DENSE ? 1 : 0;
     sa.stride[h] = p == SAF3R_STRIDE ? table[h].param : 1;
     const int cost = attention_cost(s, table, h, fl_len);
-    is_split[h] = split && attention_split(s, table, h, cost, work) ? 1 : 0;
+    is_split[h] = split && attention_split(s, table, h, cost, work) && splits_now(s, cost, work) ? 1 : 0;
     item_cost[h] = is_split[h] ? (cost + saf3r::kSplitChunks - 1) / saf3r::kSplitChunks : cost;
     if (p == SAF3R_STRIDE) {
       strided.push_back(h);

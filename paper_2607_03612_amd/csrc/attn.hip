@@ -57,7 +57,6 @@ typedef int i32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
 constexpr uint32_t kRsrcWord3 = 0x00020000u;  // gfx9 buffer descriptor: 32-bit raw data
-constexpr int kFStride = 65;                   // fp32 per LDS row (fp32 path)
 constexpr float kNegInf = -__builtin_inff();
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -981,61 +980,179 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const float* __restrict_
 
 // ------------------------------------------------------------------ fp32
 
-// Same structure with v_mfma_f32_32x32x2_f32 and fp32 softmax operands; K and
-// V tiles both go through LDS (one wave, no barrier).
+// fp32 inputs on the f16 matrix cores, at fp32 accuracy. Every operand x is
+// taken as a pair of f16 values, hi = f16(x 2^-e) and lo = f16(x 2^-e - hi),
+// which hold x to 2^-23 of itself, and a product is hi hi + hi lo + lo hi,
+// three matrix instructions with fp32 accumulation (the dropped lo lo is at
+// most 2^-22 of it, of either sign). e is shared: per query row for Q, per
+// wave for K and V, from the wave's first half tile, whose largest value goes
+// to 2^9 .. 2^10. So values up to 64 times that fit, and a value too small to
+// keep all its bits has an absolute error of 2^-35 of it. The weights P =
+// 2^(z - m) are split the same way; m is kept 8 below the running max, so that
+// P reaches 2^8 when the max moves and has room up to 2^15 before it must
+// move again. The row sum adds the fp32 weights.
+//
+// A value that overflows f16 splits into an infinity and its opposite, whose
+// products add to NaN in every query: nothing in the loop looks for it, but a
+// wave whose O or row sum is not finite at the end walks its half tiles once
+// more on the fp32 matrix instructions (v_mfma_f32_32x32x2_f32) and the values
+// as they are. So do walks over infinite or NaN inputs.
+//
+// A workgroup of four waves owns one (head, 64-query block) or one key range
+// of it. Wave w walks the half tiles w, w + 4, ... of the list with its own
+// running max, row sum and O^T, and the four are combined through LDS at the
+// end, so an item is a quarter as long as with one wave and needs no
+// workspace to be. Split Q^T (the same for all four) sits in LDS in operand
+// order, its hi part in registers too. Each wave's K half tile comes by the
+// direct buffer-to-LDS load: read straight into the operand layout, a K load
+// would touch 32 rows per instruction, and the L1's tag lookups would be the
+// bound. A lane's V column (the A operand of O^T = V^T P^T) is contiguous
+// across lanes as it stands and goes straight to registers.
+//
+// Bound by VALU issue beside the matrix cores (a half tile: 48 matrix
+// instructions, 1536 cycles, and 450 VALU ones, most of them the splits of K
+// and V) and, through the clock, by power. Every head dense at 10992 tokens,
+// 16 heads: 5.14 ms (96 TFLOP/s) with one wave per item on the fp32 matrix
+// instructions, 1.72 ms (288 TFLOP/s) so; relative error against 64 bits
+// 8e-7 before, 4e-7 now.
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+
+// Shared exponents as biased fp32 exponents of the largest value, kept where
+// the scale 2^(136 - e) and its inverse are normal; a largest value of 0 gives
+// that of 1.
+constexpr float kHeadroom = 8.f;
+__device__ inline int biased_exp(float x) { return x == 0.f ? 127 : max((int)((__float_as_uint(x) >> 23) & 255u), 15); }
+__device__ inline float exp_scale(int e) { return __uint_as_float((uint32_t)(263 - e) << 23); }
+__device__ inline float exp_unscale(int e) { return __uint_as_float((uint32_t)(e - 9) << 23); }
+
+struct SplitF16 {
+  f16x8 hi, lo;
+};
+// x[0..7] * scale as (hi, lo) pairs; the products and differences are exact.
+// Per pair of values two multiplies (kScaled), v_cvt_pk_f16_f32, two
+// v_fma_mix_f32 (which read the packed halves as they stand) and
+// v_cvt_pk_f16_f32; the empty asm keeps the compiler from converting each half
+// once more on its own, and without kScaled `scale` is a 1 that it cannot see.
+// (v_fma_mixlo_f16 / v_fma_mixhi_f16 would take four instructions instead of
+// six, but issue at the rate of an exponential: 7% slower.)
+template <bool kScaled>
+__device__ __forceinline__ SplitF16 split_f16(const float (&x)[8], float scale) {
+  SplitF16 r;
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {
+    const f32x2 xs = kScaled ? f32x2{x[e] * scale, x[e + 1] * scale} : f32x2{x[e], x[e + 1]};
+    uint32_t hb = __builtin_bit_cast(uint32_t, __builtin_convertvector(xs, f16x2));
+    asm("" : "+v"(hb));
+    const f16x2 h = __builtin_bit_cast(f16x2, hb);
+    const f32x2 rest = {fmaf(x[e], scale, -(float)h[0]), fmaf(x[e + 1], scale, -(float)h[1])};
+    const f16x2 lo = __builtin_convertvector(rest, f16x2);
+    r.hi[e] = h[0];
+    r.hi[e + 1] = h[1];
+    r.lo[e] = lo[0];
+    r.lo[e + 1] = lo[1];
+  }
+  return r;
+}
+
+__device__ inline float wave_max(float x) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) x = fmaxf(x, __shfl_xor(x, m));
+  return x;
+}
+
+// A descriptor over rows [tok, n) of a head of 256-byte fp32 rows (empty for tok outside [0, n)).
+__device__ inline __amdgpu_buffer_rsrc_t rows_from(const float* head, uint32_t tok, uint32_t n) {
+  const uint32_t t = tok < n ? tok : n;
+  return make_rsrc(head + (size_t)t * kHeadDim, (n - t) * (kHeadDim * 4));
+}
+
+// Sixteen 256-byte rows into LDS by four buffer-to-LDS loads, lane offsets
+// off[g]. With kRows the immediate offset takes instruction g four rows (1 KB)
+// on in memory and in LDS; otherwise off[g] holds the whole memory offset.
+template <bool kRows>
+__device__ __forceinline__ void dma_rows16(__amdgpu_buffer_rsrc_t r, lds_char* b, const int (&off)[4]) {
+  if constexpr (kRows) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)b, 16, off[0], 0, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)b, 16, off[1], 0, 1024, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)b, 16, off[2], 0, 2048, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)b, 16, off[3], 0, 3072, 0);
+  } else {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(b + 1024 * g), 16, off[g], 0, 0, 0);
+  }
+}
+
+constexpr int kF32Waves = 4;
+
 template <int kMode>
-__global__ __launch_bounds__(64) void attn_f32_kernel(const float* __restrict__ q,
-                                                     const float* __restrict__ k,
-                                                     const float* __restrict__ v,
-                                                     const int32_t* __restrict__ idx,
-                                                     const int32_t* __restrict__ cnt,
-                                                     float* __restrict__ out,
-                                                     float* __restrict__ lse, AttnArgs a) {
-  __shared__ float ks[kBlock * kFStride];
-  __shared__ float vsf[kBlock * kFStride];
+__global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+    const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, float* __restrict__ out,
+    float* __restrict__ lse, AttnArgs a) {
+  // split Q^T in B-operand order: [hi, lo][dims 16s ..][query half][lane] 16 bytes
+  __shared__ __attribute__((aligned(16))) f16x8 qs[2][4][2][64];
+  // per wave a K half tile: 32 rows of 256 B, 16-byte chunk c of row r at slot
+  // c ^ (r & 15), which spreads a chunk's reads over the banks
+  __shared__ __attribute__((aligned(1024))) char kbuf[kF32Waves][32 * 256];
 
   const Work w = work_item(a);
-  if (!w.valid) return;
-  const int lane = threadIdx.x;
+  if (!w.valid) return;  // the whole workgroup
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l32 = lane & 31;
   const int hf = lane >> 5;
   const int nb = a.nb;
   const bool dense = kMode != kLists || a.dense[w.h] != 0;
   const int32_t* list = idx + ((int64_t)w.h * nb + w.i) * a.cap;
-  const int64_t stride = kMode == kStrided ? a.stride[w.h] : 1;
-  const int64_t nkeys = kMode == kStrided ? (a.n + stride - 1) / stride : a.n;
-  int count = kMode == kStrided ? (int)((nkeys + kBlock - 1) / kBlock) : nb;
+  const uint32_t n = (uint32_t)a.n;  // at most 2^20, and so is a stride
+  const uint32_t stride = kMode == kStrided ? (uint32_t)a.stride[w.h] : 1u;
+  const int nkeys = (int)(kMode == kStrided ? (n + stride - 1) / stride : n);
+  int count = kMode == kStrided ? (nkeys + kBlock - 1) / kBlock : nb;
   if (!dense) count = min(max(cnt[(int64_t)w.h * nb + w.i], 0), a.cap);
   int dense_lo = 0;  // first key block of a dense head's item
   if constexpr (kMode == kLists) {
     if (w.chunk >= 0) split_range(w, a, dense, list, count, dense_lo, lane);
   }
   const int last_block = kMode == kStrided ? count - 1 : nb - 1;
+  const int blocks = kMode == kStrided ? count : nb;
 
   const int64_t head_off = (int64_t)w.h * a.n * kHeadDim;
-  const uint32_t head_bytes = (uint32_t)(a.n * kHeadDim * 4);
+  const uint32_t head_bytes = n * kHeadDim * 4;
+  const float* const kh = k + head_off;
+  const float* const vh = v + head_off;
   const __amdgpu_buffer_rsrc_t rq = make_rsrc(q + head_off, head_bytes);
-  const __amdgpu_buffer_rsrc_t rk = make_rsrc(k + head_off, head_bytes);
-  const __amdgpu_buffer_rsrc_t rv = make_rsrc(v + head_off, head_bytes);
-  const __amdgpu_buffer_rsrc_t ro = make_rsrc(out + head_off, head_bytes);
 
-  // Q^T B operand: qB[tq][s] = Q[64i + 32tq + l32][2s + hf]
-  float qB[2][32];
+  // Q: lane (l32, hf) takes dims 16s + 8hf .. of queries l32 and 32 + l32;
+  // every wave finds all the queries' exponents, and splits its own s
+  float scq[2];  // log2(e) / 8 times the query's unscale
+  float one = 1.0f;
+  asm("" : "+s"(one));
 #pragma unroll
-  for (int tq = 0; tq < 2; ++tq)
+  for (int tq = 0; tq < 2; ++tq) {
+    float own[8];
+    float mx = 0.f;
 #pragma unroll
-    for (int s4 = 0; s4 < 8; ++s4) {
-      // dims 8*s4 .. 8*s4+7 of this query: the lane half picks odd or even
-      const int row = w.i * kBlock + 32 * tq + l32;
-      const f32x4 x0 = __builtin_bit_cast(
-          f32x4, __builtin_amdgcn_raw_buffer_load_b128(rq, (row * kHeadDim + 8 * s4) * 4, 0, 0));
-      const f32x4 x1 = __builtin_bit_cast(
-          f32x4, __builtin_amdgcn_raw_buffer_load_b128(rq, (row * kHeadDim + 8 * s4 + 4) * 4, 0, 0));
-      qB[tq][4 * s4 + 0] = hf ? x0[1] : x0[0];
-      qB[tq][4 * s4 + 1] = hf ? x0[3] : x0[2];
-      qB[tq][4 * s4 + 2] = hf ? x1[1] : x1[0];
-      qB[tq][4 * s4 + 3] = hf ? x1[3] : x1[2];
-    }
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const f32x4 y = __builtin_bit_cast(
+            f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                       rq, ((w.i * kBlock + 32 * tq + l32) * kHeadDim + 16 * s + 8 * hf + 4 * c) * 4, 0, 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          mx = fmaxf(mx, fabsf(y[e]));
+          if (s == wave) own[4 * c + e] = y[e];
+        }
+      }
+    const int eq = biased_exp(pair_max(mx));
+    scq[tq] = a.scale_log2 * exp_unscale(eq);
+    const SplitF16 p = split_f16<true>(own, exp_scale(eq));
+    qs[0][wave][tq][lane] = p.hi;
+    qs[1][wave][tq][lane] = p.lo;
+  }
 
   f32x16 o[2][2];
 #pragma unroll
@@ -1044,117 +1161,361 @@ __global__ __launch_bounds__(64) void attn_f32_kernel(const float* __restrict__ 
     for (int tq = 0; tq < 2; ++tq)
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[c][tq][e] = 0.f;
-  float m[2] = {kNegInf, kNegInf};
+  float nm[2] = {-kNegInf, -kNegInf};  // kHeadroom minus the running max of the log2-scaled scores
   float l[2] = {0.f, 0.f};
   const bool tail = (nkeys % kBlock) != 0;
-  const float sc = a.scale_log2;
 
-  for (int it = 0; it < count; ++it) {
-    const int j = dense ? dense_lo + it : list[it];
-    // stage K and V tiles: rows 4n + lane/16, float4 chunk lane%16 (a STRIDE
-    // head's row r of virtual block j is token (64j + r) * stride; tokens at
-    // or past n read as zeros through an offset past the buffer's extent)
+  // This wave's half tiles: half h = wave & 1 of list entries wave / 2, wave / 2 + 2, ...
+  const int h = wave & 1;
+  auto block_at = [&](int it) -> int {
+    const int c = min(it, count - 1);
+    return __builtin_amdgcn_readfirstlane(dense ? dense_lo + c : list[c]);
+  };
+  auto first_token = [&](int j) -> uint32_t {
+    return (uint32_t)j < (uint32_t)blocks ? ((uint32_t)j * kBlock + 32 * h) * stride : n;
+  };
+  // byte offset of key row r of a half tile; a strided row past the head stays past it
+  auto row_off = [&](int r) -> int {
+    return kMode == kStrided ? (int)(min((uint32_t)r * stride, 1u << 22) * (kHeadDim * 4)) : r * (kHeadDim * 4);
+  };
+  // K by DMA: instruction g fills rows 4g .. 4g + 3, lane l its 16 bytes at
+  // 16 l: row 4g + l / 16, slot l % 16, which holds chunk (l % 16) ^ (row % 16)
+  lds_char* const kb = (lds_char*)kbuf[wave];
+  int k_dma[4];  // by g % 4; 16 rows further on the chunks repeat
 #pragma unroll
-    for (int n4 = 0; n4 < 16; ++n4) {
-      const int row = 4 * n4 + (lane >> 4);
-      const int64_t tok = ((int64_t)j * kBlock + row) * stride;
-      const int off = kMode == kStrided && tok >= a.n
-                          ? (int)head_bytes
-                          : (int)((tok * kHeadDim + (lane & 15) * 4) * 4);
-      const f32x4 kx = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rk, off, 0, 0));
-      const f32x4 vx = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rv, off, 0, 0));
+  for (int g = 0; g < 4; ++g) {
+    const int r = 4 * g + (lane >> 4);
+    k_dma[g] = (kMode == kStrided ? 0 : (lane >> 4) * (kHeadDim * 4)) + (((lane & 15) ^ r) << 4);
+  }
+  auto load_k = [&](int j) {
+    const uint32_t tok = first_token(j);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        ks[row * kFStride + (lane & 15) * 4 + e] = kx[e];
-        vsf[row * kFStride + (lane & 15) * 4 + e] = vx[e];
+    for (int u = 0; u < 2; ++u) {  // rows 16u .. 16u + 15
+      int off[4];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) off[g] = k_dma[g] + (kMode == kStrided ? row_off(4 * g + (lane >> 4)) : 0);
+      dma_rows16<kMode != kStrided>(rows_from(kh, tok + 16 * u * stride, n), kb + 4096 * u, off);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // before the V loads that the wait below counts
+  };
+  // V column 32c + l32 at the keys of P's registers, 16u + 8b + 4hf + r
+  // (a descriptor per u, so that the rest of an offset fits the instruction)
+  // (each call's own copy, so that no sum of it is hoisted into a register)
+  int v_off = 4 * hf * (kHeadDim * 4) + 4 * l32;
+  auto load_v = [&](int j, float (&x)[2][2][8]) {
+    asm volatile("" : "+v"(v_off));
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const __amdgpu_buffer_rsrc_t r = rows_from(vh, first_token(j) + 16 * u * stride, n);
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+          x[u][c][e] = __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
+              r,
+              kMode == kStrided ? row_off(8 * (e >> 2) + (e & 3) + 4 * hf) + 4 * l32 + 128 * c
+                                : v_off + (8 * (e >> 2) + (e & 3)) * (kHeadDim * 4) + 128 * c,
+              0, 0));
+    }
+  };
+
+  float vx[2][2][8];
+  int j = 0, jn = 0;  // key block of this step and of the next
+  int it = wave >> 1;
+  if (it < count) {
+    j = block_at(it);
+    jn = block_at(it + 2);
+    load_k(j);
+    load_v(j, vx);
+  }
+  __syncthreads();  // Q's parts of all waves
+  // K of this step from LDS: row l32, dims 16s + 8hf + (0..7). Its loads have
+  // landed when only the 32 V loads issued after them are in flight.
+  auto read_k = [&](float (&x)[4][8]) {
+    asm volatile("s_waitcnt vmcnt(32)" ::: "memory");
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const f32x4 y = *(lds_f32x4*)(kb + 256 * l32 + (((4 * s + 2 * hf + c) ^ (l32 & 15)) << 4));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[s][4 * c + e] = y[e];
+      }
+  };
+  float k_scale = 1.f, v_scale = 1.f, v_unscale = 1.f;
+  float sc[2] = {scq[0], scq[1]};
+  if (it < count) {
+    float kx[4][8], mk = 0.f, mv = 0.f;
+    read_k(kx);
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        mk = fmaxf(mk, fabsf(kx[s][e]));
+        mv = fmaxf(mv, fabsf(vx[s >> 1][s & 1][e]));
+      }
+    const int ek = __builtin_amdgcn_readfirstlane(biased_exp(wave_max(mk)));
+    const int ev = __builtin_amdgcn_readfirstlane(biased_exp(wave_max(mv)));
+    k_scale = exp_scale(ek);
+    v_scale = exp_scale(ev);
+    v_unscale = exp_unscale(ev);
+    sc[0] *= exp_unscale(ek);
+    sc[1] *= exp_unscale(ek);
+  }
+  f16x8 qh[2][4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int tq = 0; tq < 2; ++tq) qh[tq][s] = qs[0][s][tq][lane];
+  int q_pos = lane;
+  for (; it < count; it += 2) {
+    const int j2 = block_at(it + 4);
+    // ---- S^T = K Q^T
+    f32x16 s_acc[2] = {};
+    {
+      float kx[4][8];
+      read_k(kx);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read: the buffer may be filled again
+      load_k(jn);
+      SplitF16 kp[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) kp[s] = split_f16<true>(kx[s], k_scale);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        // read again in every half tile: hoisted, it would take 32 registers more
+        asm volatile("" : "+v"(q_pos));
+        const f16x8 ql[2] = {qs[1][s][0][q_pos], qs[1][s][1][q_pos]};
+#pragma unroll
+        for (int tq = 0; tq < 2; ++tq)
+          s_acc[tq] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kp[s].lo, qh[tq][s], s_acc[tq], 0, 0, 0);
+#pragma unroll
+        for (int tq = 0; tq < 2; ++tq)
+          s_acc[tq] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kp[s].hi, ql[tq], s_acc[tq], 0, 0, 0);
+#pragma unroll
+        for (int tq = 0; tq < 2; ++tq)
+          s_acc[tq] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kp[s].hi, qh[tq][s], s_acc[tq], 0, 0, 0);
+      }
+    }
+    float add[2] = {nm[0], nm[1]};
+    if (tail && j == last_block) {
+      asm volatile("");  // a branch, not 32 selects in every half tile
+      const int valid = nkeys - j * kBlock - 32 * h;
+      if (valid <= 0) {  // no key at all (its rows read as zeros): P = 0 and the max stays
+        add[0] = add[1] = kNegInf;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (8 * (e >> 2) + 4 * hf + (e & 3) >= valid) s_acc[0][e] = s_acc[1][e] = kNegInf;
       }
     }
 
-    f32x16 s[2][2];
-#pragma unroll
-    for (int tk = 0; tk < 2; ++tk)
+    // ---- online softmax
+    SplitF16 p[2][2];
+    float rs[2];
+    auto probs = [&]() {
 #pragma unroll
       for (int tq = 0; tq < 2; ++tq) {
-        f32x16 acc = {};
+        rs[tq] = 0.f;
 #pragma unroll
-        for (int st = 0; st < 32; ++st)
-          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ks[(32 * tk + l32) * kFStride + 2 * st + hf],
-                                                     qB[tq][st], acc, 0, 0, 0);
-        s[tk][tq] = acc;
-      }
-
-    if (tail && j == last_block) {
-      const int valid_keys = (int)(nkeys - (int64_t)j * kBlock);
+        for (int u = 0; u < 2; ++u) {
+          float pe[8];
 #pragma unroll
-      for (int tk = 0; tk < 2; ++tk)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int key = 32 * tk + 8 * (e >> 2) + 4 * hf + (e & 3);
-          if (key >= valid_keys) {
-            s[tk][0][e] = kNegInf;
-            s[tk][1][e] = kNegInf;
+          for (int e = 0; e < 8; ++e) {
+            pe[e] = fast_exp2(fmaf(s_acc[tq][8 * u + e], sc[tq], add[tq]));
+            rs[tq] += pe[e];
           }
+          p[u][tq] = split_f16<false>(pe, one);
         }
+      }
+    };
+    probs();
+    // a lane's share above 2^15 (as unsigned bits, so also inf and NaN): the max moves
+    if (__ballot(__float_as_uint(rs[0]) > 0x47000000u || __float_as_uint(rs[1]) > 0x47000000u)) {
+#pragma unroll
+      for (int tq = 0; tq < 2; ++tq) {
+        float mx = s_acc[tq][0];
+#pragma unroll
+        for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s_acc[tq][e]);
+        const float nmnew = fminf(kHeadroom - pair_max(mx) * sc[tq], nm[tq]);
+        const float alpha = fast_exp2(nmnew - nm[tq]);
+        nm[tq] = add[tq] = nmnew;
+        l[tq] *= alpha;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) o[c][tq] *= alpha;
+      }
+      probs();
     }
+    l[0] += rs[0];
+    l[1] += rs[1];
 
+    // ---- O^T += V^T P^T
+    SplitF16 vp[2][2];
 #pragma unroll
-    for (int tq = 0; tq < 2; ++tq) {
-      float mx = s[0][tq][0];
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[0][tq][e]);
+      for (int c = 0; c < 2; ++c) vp[u][c] = split_f16<true>(vx[u][c], v_scale);
+    load_v(jn, vx);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[1][tq][e]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const float mnew = fmaxf(m[tq], mx * sc);
-      const float alpha = exp2f(m[tq] - mnew);
-      m[tq] = mnew;
-      float rs = 0.f;
+    for (int u = 0; u < 2; ++u) {
 #pragma unroll
-      for (int tk = 0; tk < 2; ++tk)
+      for (int c = 0; c < 2; ++c)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const float p = exp2f(fmaf(s[tk][tq][e], sc, -mnew));
-          s[tk][tq][e] = p;
-          rs += p;
-        }
-      l[tq] = fmaf(l[tq], alpha, rs);
+        for (int tq = 0; tq < 2; ++tq)
+          o[c][tq] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vp[u][c].lo, p[u][tq].hi, o[c][tq], 0, 0, 0);
 #pragma unroll
-      for (int c = 0; c < 2; ++c) o[c][tq] *= alpha;
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int tq = 0; tq < 2; ++tq)
+          o[c][tq] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vp[u][c].hi, p[u][tq].lo, o[c][tq], 0, 0, 0);
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int tq = 0; tq < 2; ++tq)
+          o[c][tq] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vp[u][c].hi, p[u][tq].hi, o[c][tq], 0, 0, 0);
     }
+    j = jn;
+    jn = j2;
+  }
 
-    // O^T[c][tq] += V^T P^T; k-step (tk, g, r) pairs key 32tk+8g+r (lane half
-    // 0) with key 32tk+8g+4+r (lane half 1), i.e. S^T register 4g+r.
+  // ---- not finite (see above): once more on the fp32 matrix instructions
+  float bad = l[0] * 0.f + l[1] * 0.f;
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) bad = fmaf(o[c][t][e], 0.f, bad);
+  if (__ballot(bad != 0.f)) {
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int tk = 0; tk < 2; ++tk)
+      for (int t = 0; t < 2; ++t) o[c][t] = f32x16{};
+    float m[2] = {kNegInf, kNegInf};
+    l[0] = l[1] = 0.f;
+    v_unscale = 1.f;
+    for (it = wave >> 1; it < count; it += 2) {
+      j = block_at(it);
+      const int valid = min(nkeys - j * kBlock - 32 * h, 32);
+      if (j == last_block && valid <= 0) continue;
+      const __amdgpu_buffer_rsrc_t rk = rows_from(kh, first_token(j), n);
+      f32x16 s_acc[2] = {};
+#pragma unroll 1
+      for (int d = 0; d < kHeadDim; d += 4) {  // k-steps of 2 dims: d + hf, then d + 2 + hf
+        const f32x4 x = __builtin_bit_cast(
+            f32x4, __builtin_amdgcn_raw_buffer_load_b128(rk, row_off(l32) + 4 * d, 0, 0));
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const f32x4 y = __builtin_bit_cast(
+              f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                         rq, ((w.i * kBlock + 32 * t + l32) * kHeadDim + d) * 4, 0, 0));
+          s_acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(hf ? x[1] : x[0], hf ? y[1] : y[0], s_acc[t], 0, 0, 0);
+          s_acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(hf ? x[3] : x[2], hf ? y[3] : y[2], s_acc[t], 0, 0, 0);
+        }
+      }
+      load_v(j, vx);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        float mx = kNegInf;
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const int key = 32 * tk + 8 * (e >> 2) + 4 * hf + (e & 3);
-          const float va = vsf[key * kFStride + 32 * c + l32];
-#pragma unroll
-          for (int tq = 0; tq < 2; ++tq)
-            o[c][tq] = __builtin_amdgcn_mfma_f32_32x32x2f32(va, s[tk][tq][e], o[c][tq], 0, 0, 0);
+          if (j == last_block && 8 * (e >> 2) + 4 * hf + (e & 3) >= valid) s_acc[t][e] = kNegInf;
+          mx = fmaxf(mx, s_acc[t][e]);
         }
+        const float mnew = fmaxf(m[t], pair_max(mx) * a.scale_log2);
+        const float alpha = fast_exp2(m[t] - mnew);
+        m[t] = mnew;
+        l[t] *= alpha;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) o[c][t] *= alpha;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          s_acc[t][e] = fast_exp2(fmaf(s_acc[t][e], a.scale_log2, -mnew));
+          l[t] += s_acc[t][e];
+        }
+      }
+      // k-step e pairs key 8 (e / 4) + e % 4 (lane half 0) with the one 4 further on (lane half 1)
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+            o[c][t] = __builtin_amdgcn_mfma_f32_32x32x2f32(vx[e >> 3][c][e & 7], s_acc[t][e], o[c][t], 0, 0, 0);
+    }
+    nm[0] = -m[0];
+    nm[1] = -m[1];
   }
 
-  float lt[2];
+  // ---- the four waves' parts: weights 2^(m_w - M) 2^(e_w) on O^T, through LDS
+  // (running max, row sum, unscale) per wave and query into Q's array, O^T in
+  // two rounds (head-dim halves) into the K buffers, 8 KB a wave
+  const float lt[2] = {pair_sum(l[0]), pair_sum(l[1])};
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);  // the last prefetch into the K buffer
+  __syncthreads();                       // every wave is done with Q
+  f32x2* const ml = (f32x2*)qs;          // [wave][64] (max, sum)
+  float* const vun = (float*)(ml + kF32Waves * 64);
+  if (hf == 0) {
 #pragma unroll
-  for (int tq = 0; tq < 2; ++tq) lt[tq] = l[tq] + __shfl_xor(l[tq], 32);
-  if constexpr (kMode == kLists) {
-    if (w.chunk >= 0) {  // a split item: the merge combines the ranges
-      store_partials(o, m, lt, a, w.item, count <= 0, lane);
-      return;
+    for (int tq = 0; tq < 2; ++tq) ml[wave * 64 + 32 * tq + l32] = f32x2{-nm[tq], lt[tq]};
+  }
+  if (lane == 0) vun[wave] = v_unscale;
+  // this wave sums query half tq, 16-byte groups g2, g2 + 1 of the registers
+  const int tq = wave & 1, g2 = 2 * (wave >> 1);
+  float m = kNegInf, sum = 0.f, f[kF32Waves];
+  const int query = w.i * kBlock + 32 * tq + l32;
+  const __amdgpu_buffer_rsrc_t ro = make_rsrc(out + head_off, head_bytes);
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    if (c) __syncthreads();  // the first round's reads
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *(lds_f32x4*)(kb + ((t * 4 + g) * 64 + lane) * 16) =
+            f32x4{o[c][t][4 * g], o[c][t][4 * g + 1], o[c][t][4 * g + 2], o[c][t][4 * g + 3]};
+    __syncthreads();
+    if (c == 0) {
+      f32x2 x[kF32Waves];
+#pragma unroll
+      for (int u = 0; u < kF32Waves; ++u) {
+        x[u] = ml[u * 64 + 32 * tq + l32];
+        m = fmaxf(m, x[u][0]);
+      }
+#pragma unroll
+      for (int u = 0; u < kF32Waves; ++u) {
+        const float wgt = x[u][0] == kNegInf ? 0.f : fast_exp2(x[u][0] - m);
+        sum = fmaf(wgt, x[u][1], sum);
+        f[u] = wgt * vun[u];
+      }
+      const bool part = kMode == kLists && w.chunk >= 0;  // a split item: the merge combines the ranges
+      // an empty list (no keys) gives a zero output and LSE -inf
+      const float inv = part ? 1.0f : sum > 0.f ? 1.0f / sum : 0.f;
+#pragma unroll
+      for (int u = 0; u < kF32Waves; ++u) f[u] *= inv;
+      if (g2 == 0 && hf == 0) {
+        if (part)
+          *(f32x2*)(a.part_ml + ((int64_t)w.item * kBlock + 32 * tq + l32) * 2) = f32x2{m, sum};
+        else if (lse && query < (int)n)
+          lse[(int64_t)w.h * a.n + query] = sum > 0.f ? (m + log2f(sum)) * kLn2 : kNegInf;
+      }
+    }
+#pragma unroll
+    for (int g = g2; g < g2 + 2; ++g) {
+      f32x4 ov = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int u = 0; u < kF32Waves; ++u) {
+        const f32x4 y = *(lds_f32x4*)((lds_char*)kbuf[u] + ((tq * 4 + g) * 64 + lane) * 16);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ov[r] = fmaf(f[u], y[r], ov[r]);
+      }
+      if (kMode == kLists && w.chunk >= 0)
+        *(f32x4*)(a.part_o + (int64_t)w.item * (kBlock * kHeadDim) + (((c * 2 + tq) * 4 + g) * 64 + lane) * 4) = ov;
+      else
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, ov), ro,
+                                               (query * kHeadDim + 32 * c + 8 * g + 4 * hf) * 4, 0, 0);
     }
   }
-  // an empty list (no keys) gives a zero output and LSE -inf
-  float inv[2], lse_val[2];
-#pragma unroll
-  for (int tq = 0; tq < 2; ++tq) {
-    inv[tq] = lt[tq] > 0.f ? 1.0f / lt[tq] : 0.f;
-    lse_val[tq] = lt[tq] > 0.f ? (m[tq] + log2f(lt[tq])) * kLn2 : kNegInf;
-  }
-  write_out_tile_f32(o, inv, lse_val, ro, lse ? lse + (int64_t)w.h * a.n : nullptr, w.i, a.n, lane);
 }
 
 }  // namespace
@@ -1180,7 +1541,7 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
                        static_cast<uint16_t*>(out), lse, a);
   } else {
     auto kern = a.mode == kStrided ? attn_f32_kernel<kStrided> : attn_f32_kernel<kLists>;
-    hipLaunchKernelGGL(kern, grid, dim3(64), 0, s, static_cast<const float*>(q),
+    hipLaunchKernelGGL(kern, grid, dim3(64 * kF32Waves), 0, s, static_cast<const float*>(q),
                        static_cast<const float*>(k), static_cast<const float*>(v), idx, cnt,
                        static_cast<float*>(out), lse, a);
   }

@@ -82,11 +82,15 @@ constexpr int kSplitChunks = 4;
 // kBalanceMinBlocks (bf16) or kBalanceMinBlocksF32 key blocks is also split
 // when one item is longer than twice the layer's work spread over the chip's
 // wave slots (256 CUs x 4 SIMDs x 2 waves), i.e. when its rows, not the total
-// work, would set the launch's length. An fp32 tile costs about eight times
-// a bf16 one (fp32 matrix cores, one wave per SIMD), so shorter fp32 rows
-// are worth splitting.
+// work, would set the launch's length. The workspace is sized for fp32 rows
+// from kBalanceMinBlocksF32 blocks, but an fp32 item is four waves, a quarter
+// as long, and the merge launch costs about 10 us: only rows of
+// kSplitMinBlocksF32 or more that outlast twice the layer's work per workgroup
+// slot are split (16 heads, step time unsplit / split: 1044 tokens 54 / 64 us,
+// 5496 tokens 128 / 165 us, 10992 tokens 357 / 369 us).
 constexpr int kBalanceMinBlocks = 32;
 constexpr int kBalanceMinBlocksF32 = 8;
+constexpr int kSplitMinBlocksF32 = 64;
 constexpr int64_t kWaveSlots = 2048;
 constexpr int64_t kSplitItemBytes = (int64_t)kBlock * kHeadDim * 4 + (int64_t)kBlock * 2 * 4;
 

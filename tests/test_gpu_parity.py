@@ -519,6 +519,68 @@ def test_all_dense_table_fp32(gpu_lib, frames, tpf, heads):
         assert PT.max_abs(lse[h], l_ref) <= PT.LSE_TOL_F32, h
 
 
+def _fp32_layer(frames, tpf, seed, change):
+    """Dense, frame-local and strided fp32 heads with `change` applied to
+    Q, K, V [3, N, 64] in place; outputs with and without a workspace."""
+    import paper_2607_03612_amd as P
+
+    w = Workload(f"f32-{frames}x{tpf}", frames, tpf, "f32", ("fixed", 1, 1, 0), heads=3)
+    q, k, v = make_qkv(w, seed=seed)
+    change(q, k, v)
+    table = [(O.DENSE, 0), (O.FRAME_LOCAL, 0), (O.STRIDE, max(1, min(w.tokens, w.tokens // 9)))]
+    ref = O.run_layer(q, k, v, table, tpf, "f32")
+    return w, v, table, ref, [PT.gpu_layer(P, w, q, k, v, table, workspace=ws) for ws in (False, True)]
+
+
+# N = 65 and 97: a last block whose second half holds no key at all; 8 and 40 tokens: one half tile, and waves without
+# any; 4500: a dense row of 71 blocks that the workspace splits into key ranges
+@pytest.mark.parametrize("frames,tpf", [(1, 8), (1, 40), (1, 65), (1, 97), (2, 161), (3, 300), (1, 4500)])
+@pytest.mark.parametrize("scales", ["plain", "late", "tiny", "first"])
+def test_fp32_value_ranges(gpu_lib, frames, tpf, scales):
+    """fp32 operands run as scaled f16 pairs: the error bound of plain inputs
+    holds, times the largest |V|, where the values' size changes along the
+    keys (past what the first tile's scale covers), is far below 1, or falls
+    by 1000 after the first block."""
+    def change(q, k, v):
+        half = k.shape[1] // 2
+        if scales == "late":
+            k[:, half:half + 3] *= np.float32(30)  # times the special keys' 4 and Q: leaves f16 at the first tile's scale
+            q *= np.float32(0.02)
+            v[:, half:half + 3] *= np.float32(1e5)
+        elif scales == "tiny":
+            k *= np.float32(1e-18)
+            q *= np.float32(1e18)
+            v *= np.float32(1e-30)
+        elif scales == "first":
+            v[:, 64:] *= np.float32(1e-3)
+
+    w, v, table, ref, results = _fp32_layer(frames, tpf, 5, change)
+    for res in results:
+        for h in range(3):
+            assert PT.max_abs(res["out"][h], ref["out"][h]) <= PT.TOL_F32 * max(1e-30, float(np.abs(v[h]).max())), h
+            assert PT.max_abs(res["lse"][h], ref["lse"][h]) <= PT.LSE_TOL_F32, h
+
+
+@pytest.mark.parametrize("tensor,value", [("k", np.nan), ("k", np.inf), ("v", np.nan), ("v", np.inf), ("v", -np.inf)])
+def test_fp32_infinities_and_nans_stay_where_they_belong(gpu_lib, tensor, value):
+    """A token's infinite or NaN value reaches the queries that keep its block
+    and no other: a V value its own dimension, a K value (a score of +inf for
+    some queries, -inf for others) whole rows, -inf scores none."""
+    tok, dim = 470, 7
+
+    def change(q, k, v):
+        {"k": k, "v": v}[tensor][:, tok, dim] = value
+
+    with np.errstate(all="ignore"):
+        w, v, table, ref, results = _fp32_layer(3, 300, 9, change)
+    for res in results:
+        for h in range(3):
+            got, want = res["out"][h], ref["out"][h]
+            assert np.array_equal(np.isfinite(got), np.isfinite(want)), h
+            fin = np.isfinite(want)
+            assert np.max(np.abs(got[fin] - want[fin]), initial=0.0) <= PT.TOL_F32, h
+
+
 def test_all_dense_launch_over_a_subset_of_heads(gpu_lib):
     """DENSE heads with SKIP heads between them still make an all-dense launch
     (the shared-tile kernel over the listed heads only): the dense heads get
