@@ -853,6 +853,50 @@ def test_cosine_lists_many_frames(gpu_lib, frames, T, ks):
                            w.nb, cap, rank=_rank(O.COSINE_TOPK, table[h][1], ref["scores"][h], i, T))
 
 
+# widths: one, two and four 16-byte vectors per lane and row, more (rows read twice), no whole vectors, and a last run
+# of 8 dimensions that is shorter (even and odd); blocks: one, whole groups of 16 and one past them, two column bands;
+# k: each scan's form; 300 frames take two passes
+@pytest.mark.parametrize("dtype,dim,frames,T,ks", [
+    ("bf16", 512, 2, 512, (1, 2)), ("bf16", 520, 3, 340, (2, 3)), ("bf16", 1024, 4, 261, (4, 1)),
+    ("bf16", 1032, 1, 129, (2, 5)), ("bf16", 2056, 2, 300, (2, 1)), ("bf16", 701, 3, 261, (1, 2)),
+    ("f32", 256, 300, 20, (1, 2)), ("f32", 260, 5, 777, (4, 5)), ("f32", 1028, 2, 300, (2, 64)),
+    ("f32", 12, 9, 3700, (2, 3)), ("f32", 3, 1, 40, (1, 2)), ("f32", 6, 1, 1100, (3, 4)),
+])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_cosine_feature_widths(gpu_lib, dtype, dim, frames, T, ks, offset):
+    """Cosine lists against the oracle over the forms of the three kernels;
+    `offset`: a workspace aligned to 8 bytes only."""
+    import torch
+
+    import paper_2607_03612_amd as P
+
+    w = Workload(f"cosw-{frames}x{T}x{dim}", frames, T, dtype, ("fixed", 1, 1, 50), heads=2)
+    f32 = _features(w.tokens, dim, frames, T, seed=dim)
+    if dtype == "bf16":
+        f_in = (f32.view(np.uint32) >> 16).astype(np.uint16)  # cut to bf16
+    else:
+        f_in = f32
+    table = [(O.COSINE_TOPK, k) for k in ks]
+    code = P.BF16 if dtype == "bf16" else P.F32
+    cap = P.index_capacity(table, frames, T, code)
+    idx = torch.full((2, w.nb, cap), -7, dtype=torch.int32, device="cuda")
+    cnt = torch.full((2, w.nb), -9, dtype=torch.int32, device="cuda")
+    words = P.cosine_workspace_bytes(frames, T, dim, 2, code) // 8
+    ws = torch.full((words + 2,), 7.0, dtype=torch.float64, device="cuda")
+    P.cosine_select(PT.to_device(f_in, dtype), table, frames, T, idx, cnt, workspace=ws[offset:offset + words])
+    torch.cuda.synchronize()
+    assert float(ws[offset + words]) == 7.0
+    res = {"idx": idx.cpu().numpy(), "cnt": cnt.cpu().numpy()}
+    feats = O.to_f64(f_in, dtype)
+    fbar = O.cosine_block_features(feats, 64)
+    sim = fbar @ fbar.T
+    for h, k in enumerate(ks):
+        for i in range(w.nb):
+            lst, margin = O.cosine_topk_row(sim[i], k, T, 64)
+            PT.check_lists(res, h, i, O.COSINE_TOPK, lst, margin, w.nb, cap,
+                           rank=_rank(O.COSINE_TOPK, k, sim, i, T))
+
+
 # ------------------------------------------------- NMSE and the profiler
 
 
