@@ -274,19 +274,31 @@ enum AttnMode { kLists = 0, kAllDense = 1, kStrided = 2 };
 
 // One 32-row half of virtual key block j of a STRIDE head: key rows
 // (64j + 32h + r) * stride, r < 32, into an LDS half buffer (same slot layout
-// as dma_half). Rows at or past token n load as zeros (offset past the
-// buffer's extent).
-__device__ inline void dma_half_strided(__amdgpu_buffer_rsrc_t r, int j, int h, lds_char* buf,
-                                        int lane, int64_t stride, int64_t n, uint32_t head_bytes) {
+// as dma_half). As there the half's first row goes into the descriptor, on the
+// scalar unit, and a lane's four offsets inside it are the same for every half
+// (StrideLaneOffsets), so a load takes no VALU instruction; rows at or past
+// token n lie past the extent and load as zeros. With per-load 64-bit row
+// arithmetic instead, every head at stride 7 took 1.47 ms at 43968 tokens and
+// 12.3 at 137400, 1.31 and 11.1 so.
+struct StrideLaneOffsets {
+  int group[4];  // rows 8g .. 8g + 7
+};
+__device__ inline StrideLaneOffsets stride_lane_offsets(int lane, uint32_t stride) {
   const int rr = lane >> 3;
   const int c = (lane & 7) ^ swz_f(rr);
+  StrideLaneOffsets o;
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    const int64_t row = ((int64_t)j * kBlock + 32 * h + 8 * g + rr) * stride;
-    const uint32_t off = row < n ? (uint32_t)(row * kHeadDim * 2) + (uint32_t)(((g & 1) ? (c ^ 4) : c) * 16)
-                                 : head_bytes;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(buf + 1024 * g), 16, (int)off, 0, 0, 0);
-  }
+  for (int g = 0; g < 4; ++g)  // a row past any head's end (at most 2^20 rows) stays past it
+    o.group[g] = (int)(min((uint32_t)(8 * g + rr) * stride, 1u << 21) * (kHeadDim * 2)) + ((g & 1) ? (c ^ 4) : c) * 16;
+  return o;
+}
+__device__ inline void dma_half_strided(const uint16_t* head, uint32_t n, uint32_t stride, int j, int h, lds_char* buf,
+                                        const StrideLaneOffsets& off) {
+  const uint32_t tok = __builtin_amdgcn_readfirstlane(min(((uint32_t)j * kBlock + 32u * h) * stride, n));
+  const __amdgpu_buffer_rsrc_t r = make_rsrc(head + (size_t)tok * kHeadDim, (n - tok) * (kHeadDim * 2));
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(buf + 1024 * g), 16, off.group[g], 0, 0, 0);
 }
 
 // Output of one query block from the O^T accumulators (register e of tile
@@ -590,14 +602,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 
   const int64_t head_off = (int64_t)w.h * a.n * kHeadDim;
   const uint32_t head_bytes = (uint32_t)(a.n * kHeadDim * 2);
-  const __amdgpu_buffer_rsrc_t rk = make_rsrc(k + head_off, head_bytes);
-  const __amdgpu_buffer_rsrc_t rv = make_rsrc(v + head_off, head_bytes);
   const __amdgpu_buffer_rsrc_t ro = make_rsrc(out + head_off, head_bytes);
   const uint16_t* const kh = k + head_off;
   const uint16_t* const vh = v + head_off;
+  StrideLaneOffsets stride_off = {};
+  if constexpr (kMode == kStrided) stride_off = stride_lane_offsets(lane, (uint32_t)stride);
   auto load_half = [&](bool is_v, int j, int h, lds_char* buf, DmaLaneOffsets off) {
     if constexpr (kMode == kStrided)
-      dma_half_strided(is_v ? rv : rk, j, h, buf, threadIdx.x, stride, a.n, head_bytes);
+      dma_half_strided(is_v ? vh : kh, (uint32_t)a.n, (uint32_t)stride, j, h, buf, stride_off);
     else
       dma_half(is_v ? vh : kh, head_bytes, nb, j, h, buf, off);
   };

@@ -581,6 +581,33 @@ def test_fp32_infinities_and_nans_stay_where_they_belong(gpu_lib, tensor, value)
             assert np.max(np.abs(got[fin] - want[fin]), initial=0.0) <= PT.TOL_F32, h
 
 
+@pytest.mark.parametrize("dtype,n", [("bf16", 1048576), ("bf16", 200003), ("f32", 1048576)])
+def test_stride_offsets_over_long_heads(gpu_lib, dtype, n):
+    """Strided rows are addressed by 32-bit offsets inside each half tile: the
+    first and last query blocks of long heads, at strides whose half tiles
+    span up to 32 times the head and whose last virtual block holds one key."""
+    import torch
+
+    import paper_2607_03612_amd as P
+
+    strides = [n, n - 1, n // 2, n // 63, n // 64, n // 65, 32768, 4099]
+    H = len(strides)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    k, v = (torch.randn((H, n, 64), device="cuda", generator=g).to(dt) for _ in range(2))
+    q = k  # heads need not differ from their keys
+    out, lse = P.sparse_attention(q, k, v, [(O.STRIDE, s) for s in strides], 1, n, want_lse=True)
+    torch.cuda.synchronize()
+    rows = np.r_[0:64, n // 128 * 64:n // 128 * 64 + 64, n - 70:n]
+    tol, lse_tol = (PT.TOL_BF16, PT.LSE_TOL_BF16) if dtype == "bf16" else (PT.TOL_F32, PT.LSE_TOL_F32)
+    for h, s in enumerate(strides):
+        pick = torch.from_numpy(rows).cuda()
+        qh, kh, vh = (x.float().cpu().numpy().astype(np.float64) for x in (q[h, pick], k[h, ::s], v[h, ::s]))
+        o_ref, l_ref = O.dense_attention(qh, kh, vh)
+        assert PT.max_abs(PT.out_to_numpy(out[h, pick]), o_ref) <= tol, s
+        assert PT.max_abs(lse[h, pick].cpu().numpy().astype(np.float64), l_ref) <= lse_tol, s
+
+
 def test_all_dense_launch_over_a_subset_of_heads(gpu_lib):
     """DENSE heads with SKIP heads between them still make an all-dense launch
     (the shared-tile kernel over the listed heads only): the dense heads get
