@@ -245,26 +245,28 @@ int64_t saf3r_select_workspace_bytes(const saf3r_problem* problem, const saf3r_h
  *   out          device [heads, N, 64] of problem->dtype
  *   lse_or_null  NULL, or device float32 [heads, N]
  *   workspace_or_null, workspace_bytes
- *                NULL: every query block of a head is one work item. A
+ *                NULL: a query block's row is walked by one workgroup, whose
+ *                four waves share it (each its own entries, combined in a
+ *                fixed order) in fp32, and in bf16 on layers that one wave
+ *                per row would leave waiting for their longest rows. A
  *                device buffer (16-byte aligned, workspace_bytes >= 0, else
  *                SAF3R_ERR_INVALID_ARGUMENT) of at least
  *                saf3r_attention_workspace_bytes(problem, table) bytes
- *                (else SAF3R_ERR_CAPACITY): heads of two kinds run as 4 items
- *                per query block, one per quarter of the key range (for L2
- *                locality, bf16 only: on layers of 4096 or more key blocks,
- *                list heads whose list can hold 384 or more key blocks; for
- *                load balance: list or dense heads whose query blocks walk
- *                at least 32 (bf16) or 8 (fp32) key blocks, more than twice
- *                the key blocks that all list and dense heads' query blocks
- *                walk, divided by 2048 wave slots; an fp32 launch splits of
- *                these only rows of 64 or more key blocks, more than twice
- *                that work divided by 512), and a second launch merges
- *                the 4 partial softmax results per query in a fixed order
- *                (results differ from the unsplit launch only by fp32
- *                rounding and the bf16 rounding of P against each range's
- *                running max). Lists that are not ascending are still read
- *                within their row. The buffer is overwritten; launches that
- *                share one must be ordered on the GPU.
+ *                (else SAF3R_ERR_CAPACITY): heads of two kinds may run as 4
+ *                items per query block, one per quarter of the key range:
+ *                (for L2 locality, bf16 only) on layers of 4096 or more key
+ *                blocks, list heads whose list can hold 384 or more key
+ *                blocks; (for load balance) list or dense heads whose rows
+ *                walk more than twice the key blocks that all list and dense
+ *                rows walk, divided by 512, and 128 (bf16) or 64 (fp32) or
+ *                more. A second launch merges the 4 partial softmax results
+ *                per query in a fixed order. A head's results differ between
+ *                these forms, which a table's other heads take part in
+ *                choosing, only by fp32 rounding and, in bf16, the rounding of
+ *                P against each part's running max. Lists that are not
+ *                ascending are still read within their row. The buffer is
+ *                overwritten; launches that share one must be ordered on the
+ *                GPU.
  * Returns SAF3R_OK, or an error with nothing enqueued. */
 saf3r_status saf3r_sparse_attention(const saf3r_problem* problem, const saf3r_head_cfg* table,
                                     const void* q, const void* k, const void* v,
@@ -277,9 +279,11 @@ saf3r_status saf3r_sparse_attention(const saf3r_problem* problem, const saf3r_he
  * saf3r_sparse_attention describes: on a bf16 layer of nb >= 4096 key
  * blocks, the FRAME_LOCAL / TOPK / ANCHOR / GLOBAL_PROBE / COSINE_TOPK heads
  * whose list can hold 384 or more key blocks (2.9 GB for 10 such heads at
- * nb = 4294); and on any layer, list or DENSE heads whose rows are long
- * against the layer's total work (the dense head of a 10992-token layer:
- * 11.6 MB); 0 if there are none; or a negative saf3r_status. */
+ * nb = 4294); and on any layer, list or DENSE heads whose rows walk at least
+ * 32 (bf16) or 8 (fp32) key blocks, more than twice the layer's divided by
+ * 2048 (the dense head of a 10992-token layer: 11.6 MB), of which a launch
+ * splits those it finds worth it; 0 if there are none; or a negative
+ * saf3r_status. */
 int64_t saf3r_attention_workspace_bytes(const saf3r_problem* problem, const saf3r_head_cfg* table);
 
 /* Workspace bytes saf3r_cosine_select needs for features of width

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <limits>
 #include <numeric>
 #include <vector>
 
@@ -83,6 +84,12 @@ int frame_local_len(const Shape& s, int i) {
   const int64_t tok_lo = (first / T) * T;
   const int64_t tok_hi = std::min<int64_t>((last / T + 1) * T, s.n) - 1;
   return (int)(tok_hi / saf3r::kBlock - tok_lo / saf3r::kBlock + 1);
+}
+
+int mean_frame_local_len(const Shape& s) {
+  int64_t sum = 0;
+  for (int i = 0; i < s.nb; ++i) sum += frame_local_len(s, i);
+  return (int)((sum + s.nb - 1) / s.nb);
 }
 
 int max_frame_local_len(const Shape& s) {
@@ -316,12 +323,45 @@ static bool attention_split(const Shape& s, const saf3r_head_cfg* table, int h, 
   return cost >= min_blocks && (int64_t)cost * saf3r::kWaveSlots > 2 * work;
 }
 
-// Which of those heads a launch does split. In bf16 all of them; an fp32 item
-// is four waves already, so only rows of kSplitMinBlocksF32 or more key blocks
-// that outlast twice the layer's work per workgroup slot (kWaveSlots / 4).
-static bool splits_now(const Shape& s, int cost, int64_t work) {
-  return s.dtype == SAF3R_BF16 ||
-         (cost >= saf3r::kSplitMinBlocksF32 && (int64_t)cost * (saf3r::kWaveSlots / 4) > 2 * work);
+// Which of those heads a launch does split: the bf16 heads split for locality,
+// and long rows that, a quarter for each of a workgroup's four waves, still
+// outlast twice the layer's work per wave slot.
+static bool splits_now(const Shape& s, const saf3r_head_cfg* table, int h, int cost, int64_t work) {
+  const bool bf16 = s.dtype == SAF3R_BF16;
+  if (bf16 && listed_class(table[h].pattern) && s.nb >= saf3r::kSplitMinExtent && cost >= saf3r::kSplitMinBlocks)
+    return true;
+  return cost >= (bf16 ? saf3r::kSplitMinWalk : saf3r::kSplitMinWalkF32) &&
+         (int64_t)cost * (saf3r::kWaveSlots / 4) > 2 * work;
+}
+
+// The heads of a bf16 launch whose rows the four waves of a workgroup share,
+// as a least cost of a row (key blocks walked); INT_MAX for none. cost[p] is a
+// head's mean row, rows[p] its work items. A launch takes about the larger of
+// its longest item and its work per wave slot, each item kItemOverhead more
+// than it walks; sharing cuts an item to a quarter and makes four of it. Of
+// the heads from the longest rows down, as many share as make that least.
+static int shared_rows_cost(const std::vector<int>& cost, const std::vector<int64_t>& rows) {
+  constexpr int kO = saf3r::kItemOverhead;
+  std::vector<int> by(cost.size());
+  std::iota(by.begin(), by.end(), 0);
+  std::sort(by.begin(), by.end(), [&](int x, int y) { return cost[x] > cost[y]; });
+  double total = 0;
+  for (size_t p = 0; p < by.size(); ++p) total += (double)rows[p] * (cost[p] + kO);
+  auto time = [&](double longest) { return std::max(longest, total / saf3r::kWaveSlots); };
+  double best = by.empty() ? 0 : time(cost[by[0]] + kO);
+  int least = std::numeric_limits<int>::max();
+  for (size_t p = 0; p < by.size(); ++p) {
+    if (cost[by[p]] < saf3r::kShareMinBlocks) break;
+    total += (double)rows[by[p]] * 3 * kO;
+    const int next = p + 1 < by.size() ? cost[by[p + 1]] : 0;
+    if (next == cost[by[p]]) continue;  // equal rows are treated alike
+    const double t = time(std::max(cost[by[0]] / 4.0 + kO, next > 0 ? (double)(next + kO) : 0.0));
+    if (t < 0.95 * best) {
+      best = t;
+      least = cost[by[p]];
+    }
+  }
+  return least;
 }
 
 int64_t saf3r_attention_workspace_bytes(const saf3r_problem* problem, const saf3r_head_cfg* table) {
@@ -379,6 +419,8 @@ saf3r_status saf3r_sparse_attention(const saf3r_problem* problem, const saf3r_he
   a.nb = s.nb;
   a.cap = cap;
   a.slab = (s.nb + 7) / 8;
+  a.slab4 = ((s.nb + 3) / 4 + 7) / 8;
+  const bool bf16 = s.dtype == SAF3R_BF16;
   a.splits = saf3r::kSplitChunks;
   a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)saf3r::kHeadDim));
   saf3r::AttnArgs sa = a;
@@ -394,7 +436,7 @@ saf3r_status saf3r_sparse_attention(const saf3r_problem* problem, const saf3r_he
     a.dense[h] = p == SAF3R_DENSE ? 1 : 0;
     sa.stride[h] = p == SAF3R_STRIDE ? table[h].param : 1;
     const int cost = attention_cost(s, table, h, fl_len);
-    is_split[h] = split && attention_split(s, table, h, cost, work) && splits_now(s, cost, work) ? 1 : 0;
+    is_split[h] = split && attention_split(s, table, h, cost, work) && splits_now(s, table, h, cost, work) ? 1 : 0;
     item_cost[h] = is_split[h] ? (cost + saf3r::kSplitChunks - 1) / saf3r::kSplitChunks : cost;
     if (p == SAF3R_STRIDE) {
       strided.push_back(h);
@@ -403,9 +445,32 @@ saf3r_status saf3r_sparse_attention(const saf3r_problem* problem, const saf3r_he
       all_dense = all_dense && p == SAF3R_DENSE;
     }
   }
-  auto by_cost = [&](int x, int y) { return item_cost[x] > item_cost[y]; };
-  std::stable_sort(listed.begin(), listed.end(), by_cost);
-  std::stable_sort(strided.begin(), strided.end(), by_cost);
+  // bf16: rows that a workgroup's waves share count a quarter in the order
+  std::vector<char> is_shared(s.heads, 0);
+  auto order = [&](std::vector<int>& heads) -> bool {
+    bool any = false;
+    if (bf16) {
+      const int mean_fl = mean_frame_local_len(s);
+      std::vector<int> cost;
+      std::vector<int64_t> rows;
+      for (int h : heads) {
+        const int mean = attention_cost(s, table, h, mean_fl);
+        cost.push_back(is_split[h] ? (mean + saf3r::kSplitChunks - 1) / saf3r::kSplitChunks : mean);
+        rows.push_back((int64_t)s.nb * (is_split[h] ? saf3r::kSplitChunks : 1));
+      }
+      const int least = shared_rows_cost(cost, rows);
+      for (size_t p = 0; p < heads.size(); ++p) {
+        if (cost[p] < least) continue;
+        is_shared[heads[p]] = 1;
+        item_cost[heads[p]] = (item_cost[heads[p]] + 3) / 4;
+        any = true;
+      }
+    }
+    std::stable_sort(heads.begin(), heads.end(), [&](int x, int y) { return item_cost[x] > item_cost[y]; });
+    return any;
+  };
+  const bool any_shared = order(listed);
+  const bool any_strided_shared = order(strided);
   saf3r::MergeArgs ma{};
   ma.n = s.n;
   ma.nb = s.nb;
@@ -414,14 +479,17 @@ saf3r_status saf3r_sparse_attention(const saf3r_problem* problem, const saf3r_he
   a.heads = (int)listed.size();
   bool any_split = false;
   for (int h : listed) any_split = any_split || is_split[h];
-  a.mode = all_dense && !any_split ? 1 : 0;  // split items run in the list mode
+  a.waves = bf16 && any_shared ? 4 : 1;
+  a.mode = all_dense && !any_split && !any_shared ? 1 : 0;  // split items and shared rows run in the list mode
   a.unit_start[0] = 0;
   for (size_t i = 0; i < listed.size(); ++i) {
     const int h = listed[i];
     a.order[i] = (int16_t)h;
     a.split_pos[i] = is_split[h] ? (int16_t)ma.n_split : (int16_t)-1;
     if (is_split[h]) ma.head[ma.n_split++] = (int16_t)h;
-    a.unit_start[i + 1] = a.unit_start[i] + a.slab * (is_split[h] ? saf3r::kSplitChunks : 1);
+    const int ranges = is_split[h] ? saf3r::kSplitChunks : 1;
+    a.unit_start[i + 1] = a.unit_start[i] + a.slab * ranges;
+    a.shared_before[i + 1] = (int16_t)(a.shared_before[i] + (is_shared[h] ? ranges : 0));
   }
   const int64_t part_o_bytes =
       (int64_t)ma.n_split * saf3r::kSplitChunks * s.nb * saf3r::kBlock * saf3r::kHeadDim * 4;
@@ -429,12 +497,14 @@ saf3r_status saf3r_sparse_attention(const saf3r_problem* problem, const saf3r_he
   a.part_ml = split ? reinterpret_cast<float*>(static_cast<char*>(workspace_or_null) + part_o_bytes)
                     : nullptr;
   sa.heads = (int)strided.size();
+  sa.waves = bf16 && any_strided_shared ? 4 : 1;
   sa.mode = 2;
   sa.unit_start[0] = 0;
   for (size_t i = 0; i < strided.size(); ++i) {
     sa.order[i] = (int16_t)strided[i];
     sa.split_pos[i] = -1;
     sa.unit_start[i + 1] = sa.unit_start[i] + sa.slab;
+    sa.shared_before[i + 1] = (int16_t)(sa.shared_before[i] + (is_shared[strided[i]] ? 1 : 0));
   }
 
   hipStream_t hs = static_cast<hipStream_t>(stream);

@@ -55,6 +55,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 
 constexpr uint32_t kRsrcWord3 = 0x00020000u;  // gfx9 buffer descriptor: 32-bit raw data
 constexpr float kNegInf = -__builtin_inff();
@@ -75,8 +76,21 @@ struct Work {
   int h, i;
   int chunk;  // key range of a split head's item, or -1
   int item;   // split item index (partials), or -1
+  bool shared;  // bf16: the workgroup's waves share the row
   bool valid;
 };
+
+// The last order position whose first unit start(pos) is at most u.
+template <typename Start>
+__device__ inline int order_position(const AttnArgs& a, int u, Start start) {
+  int lo = 0, hi = a.heads;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (start(mid) <= u) lo = mid;
+    else hi = mid;
+  }
+  return lo;
+}
 
 // Work unit u = b / 8 of order position hh covers unit_start[hh] <= u <
 // unit_start[hh + 1]: slab units per key range, key ranges in order, so the
@@ -87,15 +101,35 @@ __device__ inline Work work_item(const AttnArgs& a) {
   Work w;
   w.valid = u < a.unit_start[a.heads];
   if (!w.valid) return w;
-  int lo = 0, hi = a.heads;  // the last order position with unit_start <= u
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (a.unit_start[mid] <= u) lo = mid;
-    else hi = mid;
-  }
+  const int lo = order_position(a, u, [&](int p) { return a.unit_start[p]; });
   const int r = u - a.unit_start[lo];
   const int chunk = r / a.slab;
   const int i = xcd * a.slab + (r - chunk * a.slab);
+  w.valid = i < a.nb;
+  w.h = a.order[lo];
+  w.i = i;
+  const int sp = a.split_pos[lo];
+  w.chunk = sp >= 0 ? chunk : -1;
+  w.item = sp >= 0 ? (sp * a.splits + chunk) * a.nb + i : -1;
+  return w;
+}
+
+// The same for workgroups of four waves (bf16): a unit is four neighbouring
+// query blocks, one a wave, or, for a head whose rows are shared, one query
+// block for all four. Slabs start one XCD further on from head to head, so
+// that the short last slab is not always the same XCD's.
+__device__ inline Work work_item4(const AttnArgs& a, int wave) {
+  const int u = blockIdx.x >> 3;
+  Work w;
+  w.valid = u < unit4_start(a, a.heads);
+  if (!w.valid) return w;
+  const int lo = order_position(a, u, [&](int p) { return unit4_start(a, p); });
+  w.shared = a.shared_before[lo + 1] > a.shared_before[lo];
+  const int slab = w.shared ? a.slab : a.slab4;
+  const int r = u - unit4_start(a, lo);
+  const int chunk = r / slab;
+  const int unit = (int)((blockIdx.x + lo) & 7) * slab + (r - chunk * slab);
+  const int i = w.shared ? unit : 4 * unit + wave;
   w.valid = i < a.nb;
   w.h = a.order[lo];
   w.i = i;
@@ -361,7 +395,7 @@ struct Bf16Walk {
   int kpart[4];
   int vpart[2][2];
 
-  __device__ __forceinline__ void init(__amdgpu_buffer_rsrc_t rq, int i, int lane, float scale) {
+  __device__ __forceinline__ void init(__amdgpu_buffer_rsrc_t rq, int i, int lane, float scale, int lds_off = 0) {
     l32 = lane & 31;
     hf = lane >> 5;
     sc = scale;
@@ -382,12 +416,12 @@ struct Bf16Walk {
     tr_row = 4 * hf + ((lane & 15) >> 2);
     tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
 #pragma unroll
-    for (int st = 0; st < 4; ++st) kpart[st] = swz(l32, 2 * st + hf);
+    for (int st = 0; st < 4; ++st) kpart[st] = swz(l32, 2 * st + hf) + lds_off;
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
       for (int r8 = 0; r8 < 2; ++r8)
-        vpart[c][r8] = swz(tr_row + 8 * r8, (32 * c + tr_col) >> 3) + (tr_col & 7) * 2;
+        vpart[c][r8] = swz(tr_row + 8 * r8, (32 * c + tr_col) >> 3) + (tr_col & 7) * 2 + lds_off;
   }
 
   // S^T of a key half (32 keys x 64 queries) from an LDS K half buffer
@@ -562,29 +596,46 @@ struct Bf16Walk {
   }
 };
 
-template <int kMode>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_kernel(const uint16_t* __restrict__ q,
-                                                      const uint16_t* __restrict__ k,
-                                                      const uint16_t* __restrict__ v,
-                                                      const int32_t* __restrict__ idx,
-                                                      const int32_t* __restrict__ cnt,
-                                                      uint16_t* __restrict__ out,
-                                                      float* __restrict__ lse, AttnArgs a) {
-  // Four LDS half tiles of 32 rows: K half 0 / 1 and V half 0 / 1 of the
-  // tiles in flight. Separate objects, so the compiler sees which DMA writes
-  // can alias which reads.
-  __shared__ __attribute__((aligned(1024))) char k0_buf[32 * 128];
-  __shared__ __attribute__((aligned(1024))) char k1_buf[32 * 128];
-  __shared__ __attribute__((aligned(1024))) char v0_buf[32 * 128];
-  __shared__ __attribute__((aligned(1024))) char v1_buf[32 * 128];
+constexpr int kHalfBytes = 32 * 128;
+
+// kWaves = 1: a workgroup is one wave and one item. kWaves = 4: four waves
+// take four neighbouring query blocks, or share one row where a.shared says
+// so: wave w walks list entries w, w + 4, ... with its own running max, row
+// sum and O^T, and the four meet in LDS. With one wave per item a layer that
+// does not fill the chip lasts as long as its longest row; a launch uses this
+// form when sharing shortens it (4 frames of 1374 tokens, 16 heads: the layer
+// 79 -> 61 us; 20 frames of 1001, 12 heads, three of them dense: 640 -> 522
+// us) and the one-wave form, whose items start and end on their own, when not
+// (137400 tokens: 4.57 ms, 4.64 with four).
+template <int kMode, int kWaves>
+__device__ __forceinline__ void attn_bf16_items(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                                               const uint16_t* __restrict__ v, const int32_t* __restrict__ idx,
+                                               const int32_t* __restrict__ cnt, uint16_t* __restrict__ out,
+                                               float* __restrict__ lse, const AttnArgs& a) {
+  // Four LDS half tiles of 32 rows per wave: K half 0 / 1 and V half 0 / 1 of
+  // the tiles in flight. Separate objects, so the compiler sees which DMA
+  // writes can alias which reads; a wave's part of each goes into its lane
+  // offsets (wk.init), so reads need no more registers than with one wave.
+  __shared__ __attribute__((aligned(1024))) char k0_buf[kWaves][kHalfBytes];
+  __shared__ __attribute__((aligned(1024))) char k1_buf[kWaves][kHalfBytes];
+  __shared__ __attribute__((aligned(1024))) char v0_buf[kWaves][kHalfBytes];
+  __shared__ __attribute__((aligned(1024))) char v1_buf[kWaves][kHalfBytes];
+  __shared__ float2 ml[kWaves > 1 ? kWaves : 1][kBlock];  // shared rows: (running max, row sum) of each wave
   lds_char* const kbuf0 = (lds_char*)k0_buf;
   lds_char* const kbuf1 = (lds_char*)k1_buf;
   lds_char* const vbuf0 = (lds_char*)v0_buf;
   lds_char* const vbuf1 = (lds_char*)v1_buf;
 
-  const Work w = work_item(a);
-  if (!w.valid) return;
-  const int lane = threadIdx.x;
+  const int wave = kWaves == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lds_off = wave * kHalfBytes;
+  Work w;
+  if constexpr (kWaves == 1) w = work_item(a);
+  else w = work_item4(a, wave);
+  if (!w.valid) return;  // a wave on its own, or all four of a shared row
+  const bool shared = kWaves > 1 && w.shared;
+  // (not threadIdx.x & 63: with the mask the walk spills, and its matrix and
+  // VALU instructions no longer interleave, 10% slower)
+  const int lane = kWaves == 1 ? threadIdx.x : __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0));
   const int l32 = lane & 31;
   const int hf = lane >> 5;
   const int nb = a.nb;
@@ -600,6 +651,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     if (w.chunk >= 0) split_range(w, a, dense, list, count, dense_lo, lane);
   }
 
+  // of a shared row, this wave takes every fourth list entry
+  const int step_tiles = shared ? kWaves : 1;
+  const int first_tile = shared ? wave : 0;
+  if (shared) count = (count - wave + kWaves - 1) / kWaves;
+
   const int64_t head_off = (int64_t)w.h * a.n * kHeadDim;
   const uint32_t head_bytes = (uint32_t)(a.n * kHeadDim * 2);
   const __amdgpu_buffer_rsrc_t ro = make_rsrc(out + head_off, head_bytes);
@@ -609,23 +665,23 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   if constexpr (kMode == kStrided) stride_off = stride_lane_offsets(lane, (uint32_t)stride);
   auto load_half = [&](bool is_v, int j, int h, lds_char* buf, DmaLaneOffsets off) {
     if constexpr (kMode == kStrided)
-      dma_half_strided(is_v ? vh : kh, (uint32_t)a.n, (uint32_t)stride, j, h, buf, stride_off);
+      dma_half_strided(is_v ? vh : kh, (uint32_t)a.n, (uint32_t)stride, j, h, buf + lds_off, stride_off);
     else
-      dma_half(is_v ? vh : kh, head_bytes, nb, j, h, buf, off);
+      dma_half(is_v ? vh : kh, head_bytes, nb, j, h, buf + lds_off, off);
   };
 
   Bf16Walk<false> wk;
-  wk.init(make_rsrc(q + head_off, head_bytes), w.i, lane, a.scale_log2);
+  wk.init(make_rsrc(q + head_off, head_bytes), w.i, lane, a.scale_log2, lds_off);
 
   const DmaLaneOffsets dma_off = dma_lane_offset(lane);
   // tile of list position it, clamped to the last kept tile: loads past the
   // end of the list refetch that tile into a buffer no later step reads
   auto tile_at = [&](int it) -> int {
-    const int c = min(it, count - 1);
+    const int c = first_tile + step_tiles * min(it, count - 1);
     return dense ? dense_lo + c : list[c];
   };
 
-  if (count <= 0) {  // an empty list: no keys, zero output, LSE -inf
+  if (count <= 0 && !shared) {  // an empty list: no keys, zero output, LSE -inf
     if constexpr (kMode == kLists) {
       if (w.chunk >= 0) {  // an empty key range: statistics only, the merge skips it
         float m[2];
@@ -649,7 +705,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   }
 
   // the last (virtual) key block may hold fewer than 64 keys
-  const int last_block = kMode == kStrided ? count - 1 : nb - 1;
+  const int last_block = kMode == kStrided ? (int)((nkeys + kBlock - 1) / kBlock) - 1 : nb - 1;
   const bool tail = (nkeys % kBlock) != 0;
   const int valid_last = (int)(nkeys - (int64_t)last_block * kBlock);
 
@@ -666,6 +722,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 #pragma unroll
     for (int tq = 0; tq < 2; ++tq) p_prev[u][tq] = bf16x8{};  // P of half -1: nothing
 
+  if (count > 0) {
   int j0 = tile_at(0), j1 = tile_at(1), j2 = tile_at(2);
   {
     // prologue: S^T of half 0, then the loads steps -2 and -1 would issue
@@ -719,10 +776,72 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   step(H0{}, T{}, T{}, j0, j1, j0);
   __builtin_amdgcn_s_waitcnt(kWaitVm0);
   wk.last_step(vbuf0, vbuf1, tail && j0 == last_block ? valid_last - 32 : 32, s_cur, p_prev);
+  }
 
   float lt[2], m[2];
   wk.row_sums(lt);
   wk.running_max(m);
+  float* const lse_row = lse ? lse + (int64_t)w.h * a.n : nullptr;
+  if (shared) {
+    // the four waves' O^T (own 16 KB, the idle half tiles) and statistics meet
+    // in LDS; wave 2c + tq sums and writes tile [c][tq]
+    lds_char* const own[4] = {kbuf0 + lds_off, kbuf1 + lds_off, vbuf0 + lds_off, vbuf1 + lds_off};
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int tq = 0; tq < 2; ++tq)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *(lds_f32x4*)(own[2 * c + tq] + (g * 64 + lane) * 16) =
+              f32x4{wk.o[c][tq][4 * g], wk.o[c][tq][4 * g + 1], wk.o[c][tq][4 * g + 2], wk.o[c][tq][4 * g + 3]};
+    if (hf == 0) {
+#pragma unroll
+      for (int tq = 0; tq < 2; ++tq) ml[wave][32 * tq + l32] = float2{m[tq], lt[tq]};
+    }
+    __syncthreads();
+    const int c = wave >> 1, tq = wave & 1;
+    lds_char* const tile = wave == 0 ? kbuf0 : wave == 1 ? kbuf1 : wave == 2 ? vbuf0 : vbuf1;
+    float2 x[kWaves];
+    float mx = kNegInf, sum = 0.f;
+#pragma unroll
+    for (int u = 0; u < kWaves; ++u) {
+      x[u] = ml[u][32 * tq + l32];
+      mx = fmaxf(mx, x[u].x);
+    }
+#pragma unroll
+    for (int u = 0; u < kWaves; ++u) {
+      x[u].x = x[u].x == kNegInf ? 0.f : fast_exp2(x[u].x - mx);
+      sum = fmaf(x[u].x, x[u].y, sum);
+    }
+    const bool part = kMode == kLists && w.chunk >= 0;  // of a split row: the merge combines the ranges
+    // an empty list (no keys) gives a zero output and LSE -inf
+    const float inv = sum == 0.f ? 0.f : 1.0f / sum;
+    const int query = w.i * kBlock + 32 * tq + l32;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      f32x4 ov = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int u = 0; u < kWaves; ++u) {
+        const f32x4 y = *(lds_f32x4*)(tile + u * kHalfBytes + (g * 64 + lane) * 16);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ov[r] = fmaf(x[u].x, y[r], ov[r]);
+      }
+      if (part) {
+        *(f32x4*)(a.part_o + (int64_t)w.item * (kBlock * kHeadDim) + (((c * 2 + tq) * 4 + g) * 64 + lane) * 4) = ov;
+      } else {
+        bf16x4 ob;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ob[r] = (__bf16)(ov[r] * inv);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(i32x2, ob), ro,
+                                              (int)((query * kHeadDim + 32 * c + 8 * g + 4 * hf) * 2), 0, 0);
+      }
+    }
+    if (c == 0 && hf == 0) {
+      if (part) *(f32x2*)(a.part_ml + ((int64_t)w.item * kBlock + 32 * tq + l32) * 2) = f32x2{mx, sum};
+      else if (lse_row && query < a.n) lse_row[query] = sum == 0.f ? kNegInf : (mx + __log2f(sum)) * kLn2;
+    }
+    return;
+  }
   if constexpr (kMode == kLists) {
     if (w.chunk >= 0) {  // a split item: the merge combines the ranges
       store_partials(wk.o, m, lt, a, w.item, false, lane);
@@ -731,8 +850,23 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   }
   const float inv[2] = {1.0f / lt[0], 1.0f / lt[1]};
   const float lse_val[2] = {(m[0] + __log2f(lt[0])) * kLn2, (m[1] + __log2f(lt[1])) * kLn2};
-  write_out_tile(wk.o, inv, lse_val, kbuf0, kbuf1, ro, lse ? lse + (int64_t)w.h * a.n : nullptr, w.i,
-                 a.n, lane);
+  write_out_tile(wk.o, inv, lse_val, kbuf0 + lds_off, kbuf1 + lds_off, ro, lse_row, w.i, a.n, lane);
+}
+
+template <int kMode>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, uint16_t* __restrict__ out,
+    float* __restrict__ lse, AttnArgs a) {
+  attn_bf16_items<kMode, 1>(q, k, v, idx, cnt, out, lse, a);
+}
+
+template <int kMode>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_rows4_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, uint16_t* __restrict__ out,
+    float* __restrict__ lse, AttnArgs a) {
+  attn_bf16_items<kMode, 4>(q, k, v, idx, cnt, out, lse, a);
 }
 
 // ---- every head dense: kDenseWaves waves per workgroup sharing the K / V tiles
@@ -1029,7 +1163,6 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const float* __restrict_
 // 8e-7 before, 4e-7 now.
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 
 // Shared exponents as biased fp32 exponents of the largest value, kept where
 // the scale 2^(136 - e) and its inverse are normal; a largest value of 0 gives
@@ -1547,8 +1680,10 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
                          static_cast<uint16_t*>(out), lse, a);
       return hipGetLastError();
     }
-    auto kern = a.mode == kStrided ? attn_bf16_kernel<kStrided> : attn_bf16_kernel<kLists>;
-    hipLaunchKernelGGL(kern, grid, dim3(64), 0, s, static_cast<const uint16_t*>(q),
+    const dim3 grid4((unsigned)(8LL * unit4_start(a, a.heads)));
+    auto kern = a.waves == 1 ? (a.mode == kStrided ? attn_bf16_kernel<kStrided> : attn_bf16_kernel<kLists>)
+                             : (a.mode == kStrided ? attn_bf16_rows4_kernel<kStrided> : attn_bf16_rows4_kernel<kLists>);
+    hipLaunchKernelGGL(kern, a.waves == 1 ? grid : grid4, dim3(64 * a.waves), 0, s, static_cast<const uint16_t*>(q),
                        static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), idx, cnt,
                        static_cast<uint16_t*>(out), lse, a);
   } else {

@@ -82,15 +82,21 @@ constexpr int kSplitChunks = 4;
 // kBalanceMinBlocks (bf16) or kBalanceMinBlocksF32 key blocks is also split
 // when one item is longer than twice the layer's work spread over the chip's
 // wave slots (256 CUs x 4 SIMDs x 2 waves), i.e. when its rows, not the total
-// work, would set the launch's length. The workspace is sized for fp32 rows
-// from kBalanceMinBlocksF32 blocks, but an fp32 item is four waves, a quarter
-// as long, and the merge launch costs about 10 us: only rows of
-// kSplitMinBlocksF32 or more that outlast twice the layer's work per workgroup
-// slot are split (16 heads, step time unsplit / split: 1044 tokens 54 / 64 us,
-// 5496 tokens 128 / 165 us, 10992 tokens 357 / 369 us).
+// work, would set the launch's length. The workspace is sized by that rule; a
+// launch splits fewer heads, because the four waves of a workgroup can share a
+// row (fp32: always; bf16: where that shortens the launch) and the merge
+// launch costs about 10 us: rows of kSplitMinWalk (bf16) or kSplitMinWalkF32
+// or more blocks whose quarter outlasts twice the layer's work per wave slot
+// (fp32, 16 heads, step time unsplit / split: 1044 tokens 54 / 64 us, 5496
+// tokens 128 / 165 us, 10992 tokens 357 / 369 us; a bf16 tile takes half the
+// time of an fp32 one).
 constexpr int kBalanceMinBlocks = 32;
 constexpr int kBalanceMinBlocksF32 = 8;
-constexpr int kSplitMinBlocksF32 = 64;
+constexpr int kSplitMinWalk = 128;
+constexpr int kSplitMinWalkF32 = 64;
+// A wave's start, end and share of the combination, in key blocks' time.
+constexpr int kItemOverhead = 3;
+constexpr int kShareMinBlocks = 8;  // shorter rows are not worth four waves
 constexpr int64_t kWaveSlots = 2048;
 constexpr int64_t kSplitItemBytes = (int64_t)kBlock * kHeadDim * 4 + (int64_t)kBlock * 2 * 4;
 
@@ -100,6 +106,8 @@ struct AttnArgs {
   int32_t cap;
   int32_t heads;          // heads in this launch (entries of order[])
   int32_t slab;           // query blocks of one head handled by one XCD: ceil(nb / 8)
+  int32_t slab4;          // groups of four of them: ceil(ceil(nb / 4) / 8)
+  int32_t waves;          // bf16: waves per workgroup, 1 or 4
   int32_t mode;           // 0: lists or dense per head; 1: every head dense; 2: STRIDE heads
   int32_t splits;         // key ranges of a split head (kSplitChunks)
   float scale_log2;       // log2(e) / sqrt(64)
@@ -107,10 +115,19 @@ struct AttnArgs {
   float* part_ml;         // split items' (running max, row sum) per query
   int16_t order[kMaxHeads];        // heads of this launch, longest work item first
   int16_t split_pos[kMaxHeads];    // by order position: index among split heads, or -1
-  int32_t unit_start[kMaxHeads + 1];  // by order position: first work unit (slab units)
+  int32_t unit_start[kMaxHeads + 1];  // by order position: first work unit (slab units a key range)
+  int16_t shared_before[kMaxHeads + 1];  // four waves: key ranges of heads before it whose rows they share
   int8_t dense[kMaxHeads];    // by head index: 1 = iterate all key blocks
   int32_t stride[kMaxHeads];  // by head index: key stride of a STRIDE head
 };
+
+static_assert(sizeof(AttnArgs) <= 4096 - 64, "kernel arguments: 4 KB with the pointers beside it");
+
+// The first work unit of an order position for workgroups of four waves: a
+// key range is slab units where they share its rows, slab4 where they do not.
+__host__ __device__ inline int unit4_start(const AttnArgs& a, int pos) {
+  return a.unit_start[pos] / a.slab * a.slab4 + a.shared_before[pos] * (a.slab - a.slab4);
+}
 
 // The merge of split heads: one wave per (split head, query block).
 struct MergeArgs {

@@ -581,6 +581,65 @@ def test_fp32_infinities_and_nans_stay_where_they_belong(gpu_lib, tensor, value)
             assert np.max(np.abs(got[fin] - want[fin]), initial=0.0) <= PT.TOL_F32, h
 
 
+# rows of 8, 9, 31 and 33 blocks beside rows too short to share; dense rows beside short lists; every head dense; one
+# block (nothing to share); the workspace's key ranges over shared rows (a single dense head of 130 blocks)
+@pytest.mark.parametrize("frames,T,table", [
+    (1, 520, [(O.DENSE, 0), (O.TOPK, 8), (O.TOPK, 1), (O.STRIDE, 1)]),
+    (2, 1000, [(O.DENSE, 0), (O.TOPK, 31), (O.FRAME_LOCAL, 0), (O.ANCHOR, 1), (O.TOPK, 3)]),
+    (3, 704, [(O.DENSE, 0)] * 3), (1, 64, [(O.DENSE, 0)] * 2), (1, 8300, [(O.DENSE, 0)]),
+    (4, 1374, [(O.STRIDE, 3), (O.STRIDE, 500), (O.STRIDE, 11)]),
+])
+@pytest.mark.parametrize("workspace", [False, True])
+def test_shared_rows(gpu_lib, frames, T, table, workspace):
+    """Small bf16 layers, whose launches let four waves share long rows:
+    outputs and LSE against the oracle, on lists the waves divide unevenly."""
+    import paper_2607_03612_amd as P
+
+    w = Workload(f"shared-{frames}x{T}", frames, T, "bf16", ("fixed", 1, 1, 50), heads=len(table))
+    q, k, v = make_qkv(w, seed=11)
+    res = PT.gpu_layer(P, w, q, k, v, table, workspace=workspace)
+    ref = O.run_layer(q, k, v, table, T, "bf16")
+    for h in range(len(table)):
+        if table[h][0] in (O.TOPK, O.FRAME_LOCAL, O.ANCHOR):
+            lists = [PT.gpu_list(res, h, i) for i in range(w.nb)]
+            out_ref, lse_ref = O.attend_head(*(O.to_f64(x[h], "bf16") for x in (q, k, v)), lists, 64)
+        else:
+            out_ref, lse_ref = ref["out"][h], ref["lse"][h]
+        assert PT.max_abs(res["out"][h], out_ref) <= PT.TOL_BF16, h
+        assert PT.max_abs(res["lse"][h], lse_ref) <= PT.LSE_TOL_BF16, h
+
+
+def test_shared_rows_with_caller_lists(gpu_lib):
+    """Lists of 0 to 12 entries in rows that four waves share: waves without
+    an entry, and an empty row (zero output, LSE -inf)."""
+    import torch
+
+    import paper_2607_03612_amd as P
+
+    n, cap = 1000, 12
+    nb = -(-n // 64)
+    w = Workload("shared-lists", 1, n, "bf16", ("fixed", 1, 1, 50), heads=1)
+    q, k, v = make_qkv(w, seed=12)
+    g = np.random.default_rng(0)
+    lists = [np.sort(g.choice(nb, size=i % 13, replace=False)) for i in range(nb)]
+    idx = np.full((1, nb, cap), -1, np.int32)
+    for i, lst in enumerate(lists):
+        idx[0, i, :len(lst)] = lst
+    cnt = np.array([[len(lst) for lst in lists]], np.int32)
+    out, lse = P.sparse_attention(*(PT.to_device(x, "bf16") for x in (q, k, v)), [(O.TOPK, cap)], 1, n,
+                                  torch.from_numpy(idx).cuda(), torch.from_numpy(cnt).cuda(), want_lse=True)
+    out, lse = PT.out_to_numpy(out)[0], lse.cpu().numpy().astype(np.float64)[0]
+    qh, kh, vh = (O.to_f64(x[0], "bf16") for x in (q, k, v))
+    for i, lst in enumerate(lists):
+        r = slice(64 * i, min(64 * i + 64, n))
+        if len(lst) == 0:
+            assert (out[r] == 0).all() and np.isneginf(lse[r]).all(), i
+            continue
+        o_ref, l_ref = O.attend_block(qh, kh, vh, i, lst, 64)
+        assert PT.max_abs(out[r], o_ref) <= PT.TOL_BF16, i
+        assert PT.max_abs(lse[r], l_ref) <= PT.LSE_TOL_BF16, i
+
+
 @pytest.mark.parametrize("dtype,n", [("bf16", 1048576), ("bf16", 200003), ("f32", 1048576)])
 def test_stride_offsets_over_long_heads(gpu_lib, dtype, n):
     """Strided rows are addressed by 32-bit offsets inside each half tile: the
