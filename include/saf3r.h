@@ -173,8 +173,9 @@ saf3r_status saf3r_estimate_blocks(const saf3r_problem* problem, const saf3r_hea
  *                      launch whose workgroups keep 16 score rows in LDS (the
  *                      library allocates nothing). Otherwise device memory,
  *                      16-byte aligned, of workspace_bytes bytes, overwritten:
- *                      the TOPK scores go there as one launch, and a second
- *                      selects one row per wave at higher occupancy (faster).
+ *                      above 256 blocks the TOPK scores go there as one
+ *                      launch, and a second selects one row per wave at higher
+ *                      occupancy (faster).
  *                      It must hold at least one TOPK head's share,
  *                      saf3r_select_workspace_bytes / (number of TOPK heads);
  *                      with less than the full size the heads are done in

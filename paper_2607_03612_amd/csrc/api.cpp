@@ -211,6 +211,7 @@ saf3r_status saf3r_select_blocks(const saf3r_problem* problem, const saf3r_head_
   ta.n = s.n;
   ta.nb = s.nb;
   ta.cap = cap;
+  ta.tokens_per_frame = s.tokens_per_frame;
   saf3r::StaticArgs sa{};
   sa.n = s.n;
   sa.nb = s.nb;
@@ -237,10 +238,11 @@ saf3r_status saf3r_select_blocks(const saf3r_problem* problem, const saf3r_head_
   }
   // Without a workspace: query blocks scored per workgroup, the most (up to
   // 16) whose score rows fit in LDS; each key-block read is then shared by
-  // that many rows. With one: as many Top-K heads per pair of launches as
+  // that many rows. On small layers, which the launch's latency bounds, four,
+  // one for each wave. With one: as many Top-K heads per pair of launches as
   // the workspace holds.
   constexpr size_t kLdsBudget = 150 * 1024;
-  int rows = 16;
+  int rows = s.nb <= saf3r::kOneLaunchBlocks ? 4 : 16;
   while (rows > 1 && saf3r::topk_lds_bytes(rows, s.nb) > kLdsBudget) rows /= 2;
   ta.rows_per_group = rows;
   const size_t lds = saf3r::topk_lds_bytes(rows, s.nb);
@@ -254,12 +256,30 @@ saf3r_status saf3r_select_blocks(const saf3r_problem* problem, const saf3r_head_
     return SAF3R_ERR_UNSUPPORTED;
   }
 
+  // Beside Top-K heads the static lists, and on small layers the global-probe
+  // ones, are written by the Top-K heads' first launch.
+  auto beside = [&](int16_t head, int32_t param, int8_t pattern) {
+    const int at = ta.n_heads + ta.n_static + ta.n_global;
+    ta.head[at] = head;
+    ta.topk[at] = param;
+    ta.pattern[at] = pattern;
+  };
+  if (ta.n_heads > 0) {
+    for (; ta.n_static < sa.n_heads; ++ta.n_static)
+      beside(sa.head[ta.n_static], sa.param[ta.n_static], sa.pattern[ta.n_static]);
+    sa.n_heads = 0;
+    if (s.nb <= saf3r::kGlobalFusedBlocks) {
+      for (; ta.n_global < ga.n_heads; ++ta.n_global) beside(ga.head[ta.n_global], ga.topk[ta.n_global], 0);
+      ga.n_heads = 0;
+    }
+  }
+
   hipStream_t hs = static_cast<hipStream_t>(stream);
   hipError_t e = saf3r::launch_select_static(block_idx, block_cnt, sa, hs);
   if (e != hipSuccess) return SAF3R_ERR_HIP;
   e = saf3r::launch_select_global(q_pooled, k_pooled, block_idx, block_cnt, scores_or_null, ga, hs);
   if (e != hipSuccess) return SAF3R_ERR_HIP;
-  if (!workspace_or_null)
+  if (!workspace_or_null || s.nb <= saf3r::kOneLaunchBlocks)
     return hip_status(saf3r::launch_select_topk(q_pooled, k_pooled, block_idx, block_cnt,
                                                 scores_or_null, ta, lds, hs));
   for (int b0 = 0; b0 < ta.n_heads; b0 += batch) {
@@ -268,6 +288,12 @@ saf3r_status saf3r_select_blocks(const saf3r_problem* problem, const saf3r_head_
     for (int q = 0; q < tb.n_heads; ++q) {
       tb.head[q] = ta.head[b0 + q];
       tb.topk[q] = ta.topk[b0 + q];
+    }
+    if (b0 > 0) tb.n_static = tb.n_global = 0;
+    for (int q = 0; q < tb.n_static + tb.n_global; ++q) {
+      tb.head[tb.n_heads + q] = ta.head[ta.n_heads + q];
+      tb.topk[tb.n_heads + q] = ta.topk[ta.n_heads + q];
+      tb.pattern[tb.n_heads + q] = ta.pattern[ta.n_heads + q];
     }
     e = saf3r::launch_select_topk_ws(q_pooled, k_pooled, static_cast<uint32_t*>(workspace_or_null),
                                      block_idx, block_cnt, scores_or_null, tb, hs);

@@ -37,15 +37,33 @@ struct PoolArgs {
   int16_t head[kMaxHeads];
 };
 
+// The Top-K heads, and after them in head[] the static and the global-probe
+// heads whose lists the same launch writes.
 struct TopKArgs {
   int64_t n;
   int32_t nb;
   int32_t cap;
+  int32_t tokens_per_frame;
   int32_t rows_per_group;  // query blocks scored together by one workgroup
-  int32_t n_heads;
+  int32_t n_heads;         // Top-K heads
+  int32_t n_static;
+  int32_t n_global;        // only where nb <= kGlobalFusedBlocks
   int16_t head[kMaxHeads];
-  int32_t topk[kMaxHeads];
+  int32_t topk[kMaxHeads];   // Top-K, global: blocks kept; static: the class parameter
+  int8_t pattern[kMaxHeads];  // of the static heads
 };
+// Global-probe heads of layers up to this size go with the Top-K launch: their
+// one workgroup per head takes 6 KB + 12 bytes per block of LDS and writes
+// every row itself. 651 blocks, two such heads beside four Top-K heads: 35 us
+// for both instead of 37 + 5 and 17 one after the other.
+constexpr int kGlobalFusedBlocks = 1024;
+// Top-K rows of layers up to this size are scored and selected in one launch
+// with or without a workspace, four rows to a workgroup. Kernel time with the
+// static heads' rows, one launch / two and the static one: 17 blocks 7.9 / 15.2
+// us, 172 blocks 14.4 / 19.8; 651 blocks 61 / 51 (with a global-probe head 35),
+// 687 blocks 106 / 75. (Sixteen rows to a workgroup of 8 or 16 waves: 13 and 20
+// us at 17 blocks; two rows to one of two waves: 18 us at 172.)
+constexpr int kOneLaunchBlocks = 256;
 
 struct StaticArgs {
   int64_t n;

@@ -35,8 +35,14 @@
 // from the pooled queries (sum of n_b * qbar_b over the blocks, over N),
 // scores every key block in float64, finds the k-th largest order key exactly
 // by an 8-bit-digit radix select over the 64-bit keys, writes the kept
-// blocks ascending (keys equal to the k-th go to the lowest indices), and a
-// second launch copies that list to every query block.
+// blocks ascending (keys equal to the k-th go to the lowest indices); a digit
+// whose keys are all kept ends the search. A second launch copies that list to
+// every query block.
+//
+// Beside Top-K heads the static lists, and up to kGlobalFusedBlocks blocks the
+// global-probe lists, come from extra workgroups of the Top-K heads' first
+// launch (beside_topk), which the launches' own cost and the one workgroup per
+// global-probe head would otherwise add to.
 #include <algorithm>
 
 #include "saf3r_internal.h"
@@ -176,6 +182,18 @@ struct RowKeys {
         const int j = base + e;
         f(e, j < nb ? lds[j] : 0u);
       }
+    }
+  }
+  // the wave's keys >= t (t >= 1): few slots by ballots, whose counts the
+  // scalar unit adds, more by a count per lane and a scan
+  __device__ inline int wave_count_ge(uint32_t t) const {
+    if constexpr (MAXK == 4) {
+      int c = 0;
+#pragma unroll
+      for (int e = 0; e < MAXK; ++e) c += __popcll(__ballot(r[e] >= t));
+      return c;
+    } else {
+      return (int)wave_total(lane_count_ge(t));
     }
   }
   // this lane's keys >= t (t >= 1)
@@ -344,7 +362,7 @@ __device__ inline void select_row(RowKeys<MAXK>& row, uint32_t* lrow, int32_t* d
         for (int q = 0; q < kPackedKeys / 64; ++q) n += pk[q] >= t ? 1u : 0u;
         c = c_above + (int)wave_total(n);
       } else {
-        c = (int)wave_total(row.lane_count_ge(t));
+        c = row.wave_count_ge(t);
       }
       if (c == k) {
         exact = true;
@@ -457,6 +475,225 @@ __device__ inline void select_row(RowKeys<MAXK>& row, uint32_t* lrow, int32_t* d
   if (lane == 0) *cnt_row = out_total;
 }
 
+// The list and count of query block i of a static-pattern head (DENSE,
+// FRAME_LOCAL, ANCHOR, STRIDE), by one wave.
+__device__ inline void static_row(int pattern, int param, int h, int i, int64_t n, int nb, int cap,
+                                  int tokens_per_frame, int32_t* idx, int32_t* cnt, int lane) {
+  const int64_t row = (int64_t)h * nb + i;
+  if (pattern == kDense) {
+    if (lane == 0) cnt[row] = nb;
+    return;
+  }
+  if (pattern == kStride) {  // token-level sampling: count of 64-key groups, no list
+    const int64_t keys = (n + param - 1) / param;
+    if (lane == 0) cnt[row] = (int)((keys + kBlock - 1) / kBlock);
+    return;
+  }
+  const int64_t T = tokens_per_frame;
+  int64_t tok_lo, tok_hi;  // token range whose blocks are kept
+  if (pattern == kAnchor) {
+    tok_lo = (int64_t)param * T;
+    tok_hi = min(tok_lo + T, n) - 1;
+  } else {  // frame-local: the frames touched by block i
+    const int64_t first = (int64_t)i * kBlock;
+    const int64_t last = min(first + kBlock, n) - 1;
+    tok_lo = (first / T) * T;
+    tok_hi = min((last / T + 1) * T, n) - 1;
+  }
+  const int j_lo = (int)(tok_lo / kBlock);
+  const int len = (int)(tok_hi / kBlock) - j_lo + 1;
+  int32_t* dst = idx + row * cap;
+  for (int p = lane; p < cap; p += 64) dst[p] = p < len ? j_lo + p : -1;
+  if (lane == 0) cnt[row] = len;
+}
+
+// LDS of a global-probe head's workgroup, in one dynamic piece: order keys,
+// then (all rows written here) the kept list, the waves' probe parts, the
+// probe, the digit histogram and a few words.
+__host__ __device__ constexpr size_t global_lds_bytes(int nb, int waves, bool list) {
+  return (size_t)nb * 8 + (list ? ((size_t)nb * 4 + 15) / 16 * 16 : 0) + (size_t)waves * kHeadDim * 8 + kHeadDim * 8 +
+         256 * 4 + (size_t)waves * 8 + 16;
+}
+
+// One global-probe head by one workgroup of kWaves waves (at least four): the
+// list goes to row 0, or with kAllRows to every row.
+template <int kWaves, bool kAllRows>
+__device__ __forceinline__ void global_head(char* lds, const double* __restrict__ qp, const double* __restrict__ kpT,
+                                            int32_t* __restrict__ idx, int32_t* __restrict__ cnt,
+                                            double* __restrict__ scores, int h, int k, int64_t n, int nb, int cap) {
+  constexpr int kThreads = 64 * kWaves;
+  uint64_t* const skeys = reinterpret_cast<uint64_t*>(lds);  // [nb] order keys
+  int32_t* const list = reinterpret_cast<int32_t*>(skeys + nb);
+  double* const part = reinterpret_cast<double*>(lds + (size_t)nb * 8 + (kAllRows ? ((size_t)nb * 4 + 15) / 16 * 16 : 0));
+  double* const qbar = part + kWaves * kHeadDim;
+  uint32_t* const hist = reinterpret_cast<uint32_t*>(qbar + kHeadDim);
+  uint32_t* const wave_tot = hist + 256;  // [kWaves][2]
+  int* const sel = reinterpret_cast<int*>(wave_tot + 2 * kWaves);  // digit, keys above it, keys at it
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const double* qh = qp + (int64_t)h * nb * kHeadDim;
+  const double* kT = kpT + (int64_t)h * kHeadDim * nb;
+
+  // probe: mean of all queries = sum over blocks of (block size) * block mean,
+  // over N. Wave w sums blocks w, w + kWaves, ... in two interleaved chains;
+  // the partial sums are added in a fixed order.
+  double acc0 = 0.0, acc1 = 0.0;
+  const double last = (double)(n - (int64_t)(nb - 1) * kBlock);
+  for (int b = wave; b < nb; b += 16 * kWaves) {
+    double x[16];  // sixteen loads in flight (past the last block: it again, with weight 0), then the two chains
+#pragma unroll
+    for (int u = 0; u < 16; ++u) x[u] = qh[(int64_t)min(b + u * kWaves, nb - 1) * kHeadDim + lane];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int bu = b + u * kWaves;
+      double& acc = u & 1 ? acc1 : acc0;
+      if (bu < nb) acc = fma(bu == nb - 1 ? last : (double)kBlock, x[u], acc);
+    }
+  }
+  part[wave * kHeadDim + lane] = acc0 + acc1;
+  __syncthreads();
+  if (t < kHeadDim) {
+    double sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) sum += part[w * kHeadDim + t];
+    qbar[t] = sum / (double)n;
+  }
+  __syncthreads();
+
+  // scores of every key block, in float64 (four interleaved chains over the
+  // dimensions, added in a fixed order), kept as order keys
+  for (int j = t; j < nb; j += kThreads) {
+    double s4[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 16
+    for (int d = 0; d < kHeadDim; ++d) s4[d & 3] = fma(qbar[d], kT[(int64_t)d * nb + j], s4[d & 3]);
+    const double sj = ((s4[0] + s4[1]) + (s4[2] + s4[3])) * 0.125;  // 1/sqrt(64), exact
+    skeys[j] = order_key(sj);
+    if (scores) scores[(int64_t)h * nb * nb + j] = sj;
+  }
+  __syncthreads();
+
+  // k-th largest key, one 8-bit digit at a time from the top
+  uint64_t prefix = 0, mask = 0;
+  int remaining = k;
+  for (int shift = 56; shift >= 0; shift -= 8) {
+    if (t < 256) hist[t] = 0;
+    __syncthreads();
+    for (int j = t; j < nb; j += kThreads) {
+      const uint64_t key = skeys[j];
+      if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255], 1u);
+    }
+    __syncthreads();
+    // digit of the k-th key: the first d, from 255 down, at which the count
+    // of keys with digit >= d reaches `remaining` (a scan over the bins in
+    // descending order by the first four waves; digit 0 if none does)
+    if (t < 256) {
+      const uint32_t hv = hist[255 - t];
+      const uint32_t incl = wave_scan_incl(hv);
+      if (lane == 63) wave_tot[2 * wave] = incl;
+    }
+    __syncthreads();
+    if (t < 256) {
+      const uint32_t hv = hist[255 - t];
+      uint32_t incl = wave_scan_incl(hv);
+      for (int w = 0; w < wave; ++w) incl += wave_tot[2 * w];
+      const bool reach = (int)incl >= remaining;
+      const uint32_t prev = incl - hv;
+      // the first lane (lowest t) that reaches; t = 255 (digit 0) always takes
+      // the rest
+      const bool first = (reach && (int)prev < remaining) || (t == 255 && (int)prev < remaining && !reach);
+      if (first) {
+        sel[0] = 255 - t;
+        sel[1] = (int)prev;
+        sel[2] = (int)hv;
+      }
+    }
+    __syncthreads();
+    prefix |= (uint64_t)sel[0] << shift;
+    mask |= 0xffull << shift;
+    remaining -= sel[1];
+    // every key with this prefix is kept: the lower digits do not matter
+    const bool whole = sel[2] == remaining && prefix != 0;
+    __syncthreads();
+    if (whole) {
+      prefix -= 1;
+      remaining = 0;
+      break;
+    }
+  }
+  // prefix is the k-th largest key; keep keys above it and the `remaining`
+  // lowest-index keys equal to it, in ascending block order
+  int32_t* dst = idx + (int64_t)h * nb * cap;
+  int out_pos = 0, eq_seen = 0;
+  for (int j0 = 0; j0 < nb; j0 += kThreads) {
+    const int j = j0 + t;
+    const uint64_t key = j < nb ? skeys[j] : 0ull;
+    const bool gt = j < nb && key > prefix;
+    const bool eq = j < nb && key == prefix;
+    const uint64_t below = (1ull << lane) - 1;
+    const uint64_t eq_mask = __ballot(eq);
+    if (lane == 0) wave_tot[2 * wave] = (uint32_t)__popcll(eq_mask);
+    __syncthreads();
+    int eq_before = eq_seen + __popcll(eq_mask & below);
+    for (int w = 0; w < wave; ++w) eq_before += (int)wave_tot[2 * w];
+    const bool kept = gt || (eq && eq_before < remaining);
+    const uint64_t kept_mask = __ballot(kept);
+    if (lane == 0) wave_tot[2 * wave + 1] = (uint32_t)__popcll(kept_mask);
+    __syncthreads();
+    int pos = out_pos + __popcll(kept_mask & below);
+    for (int w = 0; w < wave; ++w) pos += (int)wave_tot[2 * w + 1];
+    if (kept && pos < cap) {
+      dst[pos] = j;
+      if constexpr (kAllRows) list[pos] = j;
+    }
+    int eq_chunk = 0, kept_chunk = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      eq_chunk += (int)wave_tot[2 * w];
+      kept_chunk += (int)wave_tot[2 * w + 1];
+    }
+    eq_seen += eq_chunk;
+    out_pos += kept_chunk;
+    __syncthreads();
+  }
+  for (int p = out_pos + t; p < cap; p += kThreads) dst[p] = -1;
+  if (t == 0) cnt[(int64_t)h * nb] = out_pos;
+  if constexpr (kAllRows) {
+    for (int i = 1 + wave; i < nb; i += kWaves)
+      for (int p = lane; p < cap; p += 64) dst[(int64_t)i * cap + p] = p < out_pos ? list[p] : -1;
+    for (int i = 1 + t; i < nb; i += kThreads) cnt[(int64_t)h * nb + i] = out_pos;
+  }
+}
+
+
+// The workgroups before and after a Top-K launch's own: one per global-probe
+// head, then the Top-K heads' (returns their index), then the static heads'
+// rows, a wave each. Returns -1 for a workgroup that has done its part here.
+template <int kWaves>
+__device__ __forceinline__ int beside_topk(char* lds, const double* qp, const double* kpT, int32_t* idx, int32_t* cnt,
+                                           double* scores, const TopKArgs& a, int topk_groups) {
+  int b = (int)blockIdx.x;
+  if (b < a.n_global) {
+    const int slot = a.n_heads + a.n_static + b;
+    global_head<kWaves, true>(lds, qp, kpT, idx, cnt, scores, a.head[slot], a.topk[slot], a.n, a.nb, a.cap);
+    return -1;
+  }
+  b -= a.n_global;
+  if (b < topk_groups) return b;
+  const int64_t wave = (int64_t)(b - topk_groups) * kWaves + (threadIdx.x >> 6);
+  if (wave < (int64_t)a.n_static * a.nb) {
+    const int slot = a.n_heads + (int)(wave / a.nb);
+    static_row(a.pattern[slot], a.topk[slot], a.head[slot], (int)(wave % a.nb), a.n, a.nb, a.cap, a.tokens_per_frame,
+               idx, cnt, threadIdx.x & 63);
+  }
+  return -1;
+}
+// Workgroups beside a Top-K launch's own, and the LDS they need.
+inline unsigned beside_groups(const TopKArgs& a, int waves) {
+  return (unsigned)(a.n_global + ((int64_t)a.n_static * a.nb + waves - 1) / waves);
+}
+inline size_t beside_lds(const TopKArgs& a, int waves) {
+  return a.n_global > 0 ? global_lds_bytes(a.nb, waves, true) : 0;
+}
+
 template <int R, int THREADS, int MAXK>
 __global__ __launch_bounds__(THREADS) void select_topk_kernel(const double* __restrict__ qp,
                                                              const double* __restrict__ kpT,
@@ -468,8 +705,10 @@ __global__ __launch_bounds__(THREADS) void select_topk_kernel(const double* __re
   constexpr int kWaves = THREADS / 64;
   const int nb = a.nb;
   const int groups = (nb + R - 1) / R;
-  const int slot = blockIdx.x / groups;
-  const int i0 = (blockIdx.x - slot * groups) * R;
+  const int unit = beside_topk<kWaves>(reinterpret_cast<char*>(lds), qp, kpT, idx, cnt, scores, a, groups * a.n_heads);
+  if (unit < 0) return;
+  const int slot = unit / groups;
+  const int i0 = (unit - slot * groups) * R;
   const int rows = min(R, nb - i0);
   const int h = a.head[slot];
   const int k = a.topk[slot];
@@ -526,11 +765,14 @@ constexpr int kScoreWaves = 8;
 
 __global__ __launch_bounds__(kScoreWaves * 64) void topk_score_kernel(
     const double* __restrict__ qp, const double* __restrict__ kpT, uint32_t* __restrict__ keys,
-    double* __restrict__ scores, TopKArgs a) {
+    int32_t* __restrict__ idx, int32_t* __restrict__ cnt, double* __restrict__ scores, TopKArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char beside_lds_[];
   const int nb = a.nb;
   const int groups = (nb + 15) / 16;
-  const int slot = blockIdx.x / groups;
-  const int i0 = (blockIdx.x - slot * groups) * 16;
+  const int unit = beside_topk<kScoreWaves>(beside_lds_, qp, kpT, idx, cnt, scores, a, groups * a.n_heads);
+  if (unit < 0) return;
+  const int slot = unit / groups;
+  const int i0 = (unit - slot * groups) * 16;
   const int rows = min(16, nb - i0);
   const int h = a.head[slot];
   const int lane = threadIdx.x & 63;
@@ -591,45 +833,16 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(const double* __restrict
                    i & 15, a.topk[slot], nb, a.cap, lane);
 }
 
-// One wave per (head, query block) of the static-pattern heads (DENSE,
-// FRAME_LOCAL, ANCHOR, STRIDE).
+// One wave per (head, query block) of the static-pattern heads.
 __global__ __launch_bounds__(kStaticThreads) void select_static_kernel(int32_t* __restrict__ idx,
                                                                       int32_t* __restrict__ cnt,
                                                                       StaticArgs a) {
   constexpr int kWaves = kStaticThreads / 64;
-  const int lane = threadIdx.x & 63;
   const int64_t wave = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
   if (wave >= (int64_t)a.n_heads * a.nb) return;
   const int slot = (int)(wave / a.nb);
-  const int i = (int)(wave - (int64_t)slot * a.nb);
-  const int h = a.head[slot];
-  const int64_t row = (int64_t)h * a.nb + i;
-  const int pattern = a.pattern[slot];
-  if (pattern == kDense) {
-    if (lane == 0) cnt[row] = a.nb;
-    return;
-  }
-  if (pattern == kStride) {  // token-level sampling: count of 64-key groups, no list
-    const int64_t keys = (a.n + a.param[slot] - 1) / a.param[slot];
-    if (lane == 0) cnt[row] = (int)((keys + kBlock - 1) / kBlock);
-    return;
-  }
-  const int64_t T = a.tokens_per_frame;
-  int64_t tok_lo, tok_hi;  // token range whose blocks are kept
-  if (pattern == kAnchor) {
-    tok_lo = (int64_t)a.param[slot] * T;
-    tok_hi = min(tok_lo + T, a.n) - 1;
-  } else {  // frame-local: the frames touched by block i
-    const int64_t first = (int64_t)i * kBlock;
-    const int64_t last = min(first + kBlock, a.n) - 1;
-    tok_lo = (first / T) * T;
-    tok_hi = min((last / T + 1) * T, a.n) - 1;
-  }
-  const int j_lo = (int)(tok_lo / kBlock);
-  const int len = (int)(tok_hi / kBlock) - j_lo + 1;
-  int32_t* dst = idx + row * a.cap;
-  for (int p = lane; p < a.cap; p += 64) dst[p] = p < len ? j_lo + p : -1;
-  if (lane == 0) cnt[row] = len;
+  static_row(a.pattern[slot], a.param[slot], a.head[slot], (int)(wave - (int64_t)slot * a.nb), a.n, a.nb, a.cap,
+             a.tokens_per_frame, idx, cnt, threadIdx.x & 63);
 }
 
 // The list check: result[0] counts failing rows, result[1] keeps the lowest
@@ -681,136 +894,9 @@ __global__ __launch_bounds__(kGlobalThreads) void select_global_kernel(const dou
                                                                       int32_t* __restrict__ cnt,
                                                                       double* __restrict__ scores,
                                                                       GlobalArgs a) {
-  extern __shared__ __attribute__((aligned(16))) uint64_t skeys[];  // [nb] order keys
-  __shared__ double part[kGlobalWaves][kHeadDim];
-  __shared__ double qbar[kHeadDim];
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t wave_tot[kGlobalWaves][2];
-  __shared__ int sel_digit, sel_above;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int h = a.head[blockIdx.x];
-  const int k = a.topk[blockIdx.x];
-  const int nb = a.nb;
-  const double* qh = qp + (int64_t)h * nb * kHeadDim;
-  const double* kT = kpT + (int64_t)h * kHeadDim * nb;
-
-  // probe: mean of all queries = sum over blocks of (block size) * block mean,
-  // over N. Wave w sums blocks w, w + 16, ... in two interleaved chains; the
-  // partial sums are added in a fixed order.
-  double acc0 = 0.0, acc1 = 0.0;
-  int b = wave;
-  for (; b + 7 * kGlobalWaves < nb; b += 8 * kGlobalWaves) {
-    double x[8];  // eight loads in flight, then the two chains
-#pragma unroll
-    for (int u = 0; u < 8; ++u) x[u] = qh[(int64_t)(b + u * kGlobalWaves) * kHeadDim + lane];
-#pragma unroll
-    for (int u = 0; u < 8; u += 2) {
-      acc0 = fma((double)kBlock, x[u], acc0);
-      const int b1 = b + (u + 1) * kGlobalWaves;
-      const double n1 = b1 == nb - 1 ? (double)(a.n - (int64_t)(nb - 1) * kBlock) : (double)kBlock;
-      acc1 = fma(n1, x[u + 1], acc1);
-    }
-  }
-  for (; b < nb; b += kGlobalWaves) {
-    const double n0 = b == nb - 1 ? (double)(a.n - (int64_t)(nb - 1) * kBlock) : (double)kBlock;
-    acc0 = fma(n0, qh[(int64_t)b * kHeadDim + lane], acc0);
-  }
-  part[wave][lane] = acc0 + acc1;
-  __syncthreads();
-  if (t < kHeadDim) {
-    double sum = 0.0;
-#pragma unroll
-    for (int w = 0; w < kGlobalWaves; ++w) sum += part[w][t];
-    qbar[t] = sum / (double)a.n;
-  }
-  __syncthreads();
-
-  // scores of every key block, in float64 (four interleaved chains over the
-  // dimensions, added in a fixed order), kept as order keys
-  for (int j = t; j < nb; j += kGlobalThreads) {
-    double s4[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int d = 0; d < kHeadDim; ++d) s4[d & 3] = fma(qbar[d], kT[(int64_t)d * nb + j], s4[d & 3]);
-    const double sj = ((s4[0] + s4[1]) + (s4[2] + s4[3])) * 0.125;  // 1/sqrt(64), exact
-    skeys[j] = order_key(sj);
-    if (scores) scores[(int64_t)h * nb * nb + j] = sj;
-  }
-  __syncthreads();
-
-  // k-th largest key, one 8-bit digit at a time from the top
-  uint64_t prefix = 0, mask = 0;
-  int remaining = k;
-  for (int shift = 56; shift >= 0; shift -= 8) {
-    if (t < 256) hist[t] = 0;
-    __syncthreads();
-    for (int j = t; j < nb; j += kGlobalThreads) {
-      const uint64_t key = skeys[j];
-      if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255], 1u);
-    }
-    __syncthreads();
-    // digit of the k-th key: the first d, from 255 down, at which the count
-    // of keys with digit >= d reaches `remaining` (a scan over the bins in
-    // descending order by the first four waves; digit 0 if none does)
-    if (t < 256) {
-      const uint32_t hv = hist[255 - t];
-      const uint32_t incl = wave_scan_incl(hv);
-      if (lane == 63) wave_tot[wave][0] = incl;
-    }
-    __syncthreads();
-    if (t < 256) {
-      const uint32_t hv = hist[255 - t];
-      uint32_t incl = wave_scan_incl(hv);
-      for (int w = 0; w < wave; ++w) incl += wave_tot[w][0];
-      const bool reach = (int)incl >= remaining;
-      const uint32_t prev = incl - hv;
-      // the first lane (lowest t) that reaches; t = 255 (digit 0) always takes
-      // the rest
-      const bool first = (reach && (int)prev < remaining) || (t == 255 && (int)prev < remaining && !reach);
-      if (first) {
-        sel_digit = 255 - t;
-        sel_above = (int)prev;
-      }
-    }
-    __syncthreads();
-    prefix |= (uint64_t)sel_digit << shift;
-    mask |= 0xffull << shift;
-    remaining -= sel_above;
-    __syncthreads();
-  }
-  // prefix is the k-th largest key; keep keys above it and the `remaining`
-  // lowest-index keys equal to it, in ascending block order
-  int32_t* dst = idx + (int64_t)h * nb * a.cap;
-  int out_pos = 0, eq_seen = 0;
-  for (int j0 = 0; j0 < nb; j0 += kGlobalThreads) {
-    const int j = j0 + t;
-    const uint64_t key = j < nb ? skeys[j] : 0ull;
-    const bool gt = j < nb && key > prefix;
-    const bool eq = j < nb && key == prefix;
-    const uint64_t below = (1ull << lane) - 1;
-    const uint64_t eq_mask = __ballot(eq);
-    if (lane == 0) wave_tot[wave][0] = (uint32_t)__popcll(eq_mask);
-    __syncthreads();
-    int eq_before = eq_seen + __popcll(eq_mask & below);
-    for (int w = 0; w < wave; ++w) eq_before += (int)wave_tot[w][0];
-    const bool kept = gt || (eq && eq_before < remaining);
-    const uint64_t kept_mask = __ballot(kept);
-    if (lane == 0) wave_tot[wave][1] = (uint32_t)__popcll(kept_mask);
-    __syncthreads();
-    int pos = out_pos + __popcll(kept_mask & below);
-    for (int w = 0; w < wave; ++w) pos += (int)wave_tot[w][1];
-    if (kept && pos < a.cap) dst[pos] = j;
-    int eq_chunk = 0, kept_chunk = 0;
-#pragma unroll
-    for (int w = 0; w < kGlobalWaves; ++w) {
-      eq_chunk += (int)wave_tot[w][0];
-      kept_chunk += (int)wave_tot[w][1];
-    }
-    eq_seen += eq_chunk;
-    out_pos += kept_chunk;
-    __syncthreads();
-  }
-  for (int p = out_pos + t; p < a.cap; p += kGlobalThreads) dst[p] = -1;
-  if (t == 0) cnt[(int64_t)h * nb] = out_pos;
+  extern __shared__ __attribute__((aligned(16))) char glds[];
+  global_head<kGlobalWaves, false>(glds, qp, kpT, idx, cnt, scores, a.head[blockIdx.x], a.topk[blockIdx.x], a.n, a.nb,
+                                   a.cap);
 }
 
 // Copies row 0 of every global-probe head to its other query blocks: one
@@ -835,12 +921,13 @@ template <int R, int THREADS, int MAXK>
 hipError_t launch_topk(const double* qp, const double* kpT, int32_t* idx, int32_t* cnt,
                        double* scores, const TopKArgs& a, size_t lds, hipStream_t s) {
   auto kern = select_topk_kernel<R, THREADS, MAXK>;
+  lds = std::max(lds, beside_lds(a, THREADS / 64));
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   const int groups = (a.nb + R - 1) / R;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(groups * a.n_heads)), dim3(THREADS), lds, s, qp, kpT,
-                     idx, cnt, scores, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(groups * a.n_heads) + beside_groups(a, THREADS / 64)), dim3(THREADS), lds,
+                     s, qp, kpT, idx, cnt, scores, a);
   return hipGetLastError();
 }
 
@@ -875,8 +962,8 @@ hipError_t launch_select_topk_ws(const double* qp, const double* kpT, uint32_t* 
                                  int32_t* cnt, double* scores, const TopKArgs& a, hipStream_t s) {
   if (a.n_heads == 0) return hipSuccess;
   const int groups = (a.nb + 15) / 16;
-  hipLaunchKernelGGL(topk_score_kernel, dim3((unsigned)(groups * a.n_heads)),
-                     dim3(kScoreWaves * 64), 0, s, qp, kpT, keys, scores, a);
+  hipLaunchKernelGGL(topk_score_kernel, dim3((unsigned)(groups * a.n_heads) + beside_groups(a, kScoreWaves)),
+                     dim3(kScoreWaves * 64), beside_lds(a, kScoreWaves), s, qp, kpT, keys, idx, cnt, scores, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // waves per workgroup: as many rows as fit in 64 KB of LDS, at most four
@@ -903,7 +990,7 @@ hipError_t launch_select_topk_ws(const double* qp, const double* kpT, uint32_t* 
 hipError_t launch_select_global(const double* qp, const double* kpT, int32_t* idx, int32_t* cnt,
                                 double* scores, const GlobalArgs& a, hipStream_t s) {
   if (a.n_heads == 0) return hipSuccess;
-  const size_t lds = (size_t)a.nb * sizeof(uint64_t);
+  const size_t lds = global_lds_bytes(a.nb, kGlobalWaves, false);
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_global_kernel),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;

@@ -774,6 +774,56 @@ def test_global_probe_gives_every_query_block_one_list(gpu_lib):
                    rank=PT.ranking(O.GLOBAL_PROBE, 69, s))
 
 
+# one launch for all (up to 256 blocks), two with the static and the global-probe heads beside the scores (up to 1024),
+# global-probe heads on their own (above); first and last size of each
+@pytest.mark.parametrize("n", [40, 256 * 64, 256 * 64 + 1, 1024 * 64, 1024 * 64 + 1])
+def test_lists_of_heads_selected_together(gpu_lib, n):
+    """Top-K, global-probe and static heads of one table: the same lists and
+    counts without a workspace, with one for a single head and with a full
+    one, each against the oracle on sampled rows; rows of a cosine head and of
+    a skipped head stay as they were."""
+    import torch
+
+    import paper_2607_03612_amd as P
+
+    w = Workload(f"together-{n}", 1, n, "bf16", ("fixed", 1, 1, 50), heads=9)
+    nb, T = w.nb, n
+    table = [(O.STRIDE, 3), (O.TOPK, max(1, nb // 9)), (O.GLOBAL_PROBE, max(1, nb // 7)), (P.SKIP, 0), (O.DENSE, 0),
+             (O.TOPK, 1), (O.COSINE_TOPK, 1), (O.GLOBAL_PROBE, nb), (O.ANCHOR, 0)]
+    q, k, _ = make_qkv(w, seed=2)
+    tq, tk = PT.to_device(q, "bf16"), PT.to_device(k, "bf16")
+    qp, kp = P.estimate_blocks(tq, tk, table, 1, T)
+    cap = P.index_capacity(table, 1, T) + 3
+    full = P.select_workspace_bytes(table, 1, T)
+    got = []
+    for nbytes in (0, full // 2, full):
+        idx = torch.full((9, nb, cap), -7, dtype=torch.int32, device="cuda")
+        cnt = torch.full((9, nb), -9, dtype=torch.int32, device="cuda")
+        ws = torch.empty(nbytes // 4, dtype=torch.int32, device="cuda") if nbytes else None
+        P.select_blocks(qp, kp, table, 1, T, cap, idx, cnt, workspace=ws)
+        torch.cuda.synchronize()
+        got.append({"idx": idx.cpu().numpy(), "cnt": cnt.cpu().numpy()})
+    for g in got[1:]:
+        assert np.array_equal(g["idx"], got[0]["idx"]) and np.array_equal(g["cnt"], got[0]["cnt"])
+    res = got[0]
+    for h in (3, 6):
+        assert (res["idx"][h] == -7).all() and (res["cnt"][h] == -9).all()
+    assert (res["cnt"][4] == nb).all() and (res["cnt"][0] == _stride_blocks(n, 3)).all()
+    for h in (1, 2, 5, 7):
+        pattern, kk = table[h]
+        qh, kh = O.to_f64(q[h], "bf16"), O.to_f64(k[h], "bf16")
+        kbar = O.pool_blocks(kh, 64)
+        for i in sorted({0, 1, nb // 2, nb - 1} & set(range(nb))):
+            r = O.block_range(i, n, 64)
+            probe = O.pool_blocks(qh[r.start:r.stop], 64)[0] if pattern == O.TOPK else qh.mean(axis=0)
+            srow = kbar @ probe / 8
+            lst, margin = O.topk_row(srow, kk)
+            PT.check_lists(res, h, i, O.TOPK, lst, margin, nb, cap, rank=PT.ranking(O.GLOBAL_PROBE, kk, srow))
+        if pattern == O.GLOBAL_PROBE:
+            assert (res["idx"][h] == res["idx"][h][0]).all() and (res["cnt"][h] == kk).all()
+    assert (res["cnt"][8] == nb).all() and (res["idx"][8][:, :nb] == np.arange(nb)).all()
+
+
 def test_equal_scores_keep_the_lowest_block_indices(gpu_lib):
     """Every key token equal: all block scores are the same float64 value, so
     the Top-K and global-probe selections reduce to the tie rule of the
