@@ -75,27 +75,28 @@ saf3r_status check_table(const Shape& s, const saf3r_head_cfg* t) {
   return SAF3R_OK;
 }
 
-// Kept blocks of query block i of a frame-local head: the key blocks whose
-// tokens overlap the frames touched by block i (a contiguous range).
-int frame_local_len(const Shape& s, int i) {
-  const int64_t T = s.tokens_per_frame;
-  const int64_t first = (int64_t)i * saf3r::kBlock;
-  const int64_t last = std::min<int64_t>(first + saf3r::kBlock, s.n) - 1;
-  const int64_t tok_lo = (first / T) * T;
-  const int64_t tok_hi = std::min<int64_t>((last / T + 1) * T, s.n) - 1;
-  return (int)(tok_hi / saf3r::kBlock - tok_lo / saf3r::kBlock + 1);
-}
-
-int mean_frame_local_len(const Shape& s) {
-  int64_t sum = 0;
-  for (int i = 0; i < s.nb; ++i) sum += frame_local_len(s, i);
-  return (int)((sum + s.nb - 1) / s.nb);
-}
-
-int max_frame_local_len(const Shape& s) {
-  int best = 0;
-  for (int i = 0; i < s.nb; ++i) best = std::max(best, frame_local_len(s, i));
-  return best;
+// Kept blocks of a frame-local head's query blocks, the key blocks whose tokens
+// overlap the frames touched by the query block (a contiguous range): the most
+// of any query block, and the mean, rounded up. One walk over the blocks
+// without a division.
+struct FrameLocalLens {
+  int max = 0, mean = 0;
+};
+FrameLocalLens frame_local_lens(const Shape& s) {
+  const int64_t T = s.tokens_per_frame, n = s.n;
+  FrameLocalLens r;
+  int64_t sum = 0, lo = 0, hi = T;  // [lo, lo + T): the first frame touched; hi: the last one's end
+  for (int i = 0; i < s.nb; ++i) {
+    const int64_t first = (int64_t)i * saf3r::kBlock;
+    const int64_t last = std::min<int64_t>(first + saf3r::kBlock, n) - 1;
+    while (lo + T <= first) lo += T;
+    while (hi <= last) hi += T;
+    const int len = (int)((std::min(hi, n) - 1) / saf3r::kBlock - lo / saf3r::kBlock + 1);
+    r.max = std::max(r.max, len);
+    sum += len;
+  }
+  r.mean = (int)((sum + s.nb - 1) / s.nb);
+  return r;
 }
 
 // Kept blocks of an ANCHOR head: the key blocks holding a token of frame a.
@@ -128,7 +129,7 @@ int capacity(const Shape& s, const saf3r_head_cfg* t) {
     if (p == SAF3R_COSINE_TOPK) cap = std::max(cap, cosine_len(s, t[h].param));
     if (p == SAF3R_FRAME_LOCAL) any_fl = true;
   }
-  if (any_fl) cap = std::max(cap, max_frame_local_len(s));
+  if (any_fl) cap = std::max(cap, frame_local_lens(s).max);
   return cap;
 }
 
@@ -396,7 +397,7 @@ int64_t saf3r_attention_workspace_bytes(const saf3r_problem* problem, const saf3
   if (st != SAF3R_OK) return st;
   st = check_table(s, table);
   if (st != SAF3R_OK) return st;
-  const int fl_len = max_frame_local_len(s);
+  const int fl_len = frame_local_lens(s).max;
   const int64_t work = listed_work(s, table, fl_len);
   int64_t n_split = 0;
   for (int h = 0; h < s.heads; ++h)
@@ -452,7 +453,8 @@ saf3r_status saf3r_sparse_attention(const saf3r_problem* problem, const saf3r_he
   saf3r::AttnArgs sa = a;
   std::vector<int> item_cost(s.heads, 0);
   std::vector<char> is_split(s.heads, 0);
-  const int fl_len = max_frame_local_len(s);
+  const FrameLocalLens fl = frame_local_lens(s);
+  const int fl_len = fl.max;
   const int64_t work = listed_work(s, table, fl_len);
   std::vector<int> listed, strided;
   bool all_dense = true;
@@ -476,11 +478,10 @@ saf3r_status saf3r_sparse_attention(const saf3r_problem* problem, const saf3r_he
   auto order = [&](std::vector<int>& heads) -> bool {
     bool any = false;
     if (bf16) {
-      const int mean_fl = mean_frame_local_len(s);
       std::vector<int> cost;
       std::vector<int64_t> rows;
       for (int h : heads) {
-        const int mean = attention_cost(s, table, h, mean_fl);
+        const int mean = attention_cost(s, table, h, fl.mean);
         cost.push_back(is_split[h] ? (mean + saf3r::kSplitChunks - 1) / saf3r::kSplitChunks : mean);
         rows.push_back((int64_t)s.nb * (is_split[h] ? saf3r::kSplitChunks : 1));
       }
