@@ -35,6 +35,10 @@
 // query in a workspace; attn_merge_kernel combines the ranges of each query
 // block in range order.
 //
+// Where one wave per row would leave a launch waiting for its longest rows, it
+// runs attn_bf16_rows4_kernel: workgroups of four waves with the same walk,
+// which take four query blocks or share one row and combine in LDS.
+//
 // A launch in which every head is dense runs attn_bf16_dense_kernel: four
 // waves take four neighbouring query blocks of one head, and since all four
 // walk every key block in order, each K and V half tile is staged in LDS
