@@ -1160,7 +1160,7 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const float* __restrict_
 // across lanes as it stands and goes straight to registers.
 //
 // Bound by VALU issue beside the matrix cores (a half tile: 48 matrix
-// instructions, 1536 cycles, and 450 VALU ones, most of them the splits of K
+// instructions, 1536 cycles, and 380 VALU ones, most of them the splits of K
 // and V) and, through the clock, by power. Every head dense at 10992 tokens,
 // 16 heads: 5.14 ms (96 TFLOP/s) with one wave per item on the fp32 matrix
 // instructions, 1.72 ms (288 TFLOP/s) so; relative error against 64 bits
