@@ -230,9 +230,11 @@ int64_t saf3r_select_workspace_bytes(const saf3r_problem* problem, const saf3r_h
  * the log of the sum of the bf16-rounded weights exp(z_u - max) plus max: it
  * differs from the fp32 log-sum-exp by up to 2^-8 (bf16's relative rounding
  * of each weight), and a caller that merges lse across launches inherits that
- * bias. fp32 inputs: to fp32 accuracy throughout (every operand as a scaled
- * pair of f16 values on the f16 matrix cores, fp32 accumulation, softmax and
- * row sums in fp32; values outside that form's range on the fp32 ones).
+ * bias. fp32 inputs: to fp32 accuracy throughout, each output by itself
+ * (every operand as three bf16 values that hold its 24 bits, on the bf16 matrix
+ * cores, fp32 accumulation, softmax and row sums in fp32; query blocks that
+ * meet infinities or NaNs, queries from 2^90 on or, not 0, below 2^-100, or
+ * outputs below 2^-100, on the fp32 ones, which take more than twice as long).
  *   q, k, v      device [heads, N, 64] of problem->dtype
  *   block_idx, block_cnt, cap   as written by saf3r_select_blocks; entries of
  *                DENSE and STRIDE heads are not read. A list that is not

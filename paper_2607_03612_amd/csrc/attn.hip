@@ -1130,23 +1130,25 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const float* __restrict_
 
 // ------------------------------------------------------------------ fp32
 
-// fp32 inputs on the f16 matrix cores, at fp32 accuracy. Every operand x is
-// taken as a pair of f16 values, hi = f16(x 2^-e) and lo = f16(x 2^-e - hi),
-// which hold x to 2^-23 of itself, and a product is hi hi + hi lo + lo hi,
-// three matrix instructions with fp32 accumulation (the dropped lo lo is at
-// most 2^-22 of it, of either sign). e is shared: per query row for Q, per
-// wave for K and V, from the wave's first half tile, whose largest value goes
-// to 2^9 .. 2^10. So values up to 64 times that fit, and a value too small to
-// keep all its bits has an absolute error of 2^-35 of it. The weights P =
-// 2^(z - m) are split the same way; m is kept 8 below the running max, so that
-// P reaches 2^8 when the max moves and has room up to 2^15 before it must
-// move again. The row sum adds the fp32 weights.
+// fp32 inputs on the bf16 matrix cores, at fp32 accuracy. Every operand x is
+// taken as three bf16 values, hi = bf16(x), mid = bf16(x - hi) and lo =
+// x - hi - mid, which hold its 24 bits exactly and have fp32's exponent range,
+// so there is no scale and no range to leave; a product is hi hi + hi mid +
+// mid hi + mid mid + hi lo + lo hi, six matrix instructions with fp32
+// accumulation (the dropped mid lo, lo mid and lo lo are at most 2^-25 of it
+// together, below the rounding of one fp32 addition). The weights P are split
+// the same way, and the row sum adds the fp32 weights.
 //
-// A value that overflows f16 splits into an infinity and its opposite, whose
-// products add to NaN in every query: nothing in the loop looks for it, but a
-// wave whose O or row sum is not finite at the end walks its half tiles once
-// more on the fp32 matrix instructions (v_mfma_f32_32x32x2_f32) and the values
-// as they are. So do walks over infinite or NaN inputs.
+// Not exact in that form: values whose parts fall below bf16's normal range
+// (|x| < 2^-102: up to 2^-126 of them is lost), and those at the top that
+// round to an infinity. So a workgroup with a Q value in 0 < |q| < 2^-100 or
+// from 2^90 on, and a wave whose O or row sum is not finite at the end or
+// whose outputs are not 0 but below 2^-100 (all that V's lost parts could
+// matter to: with Q below 2^90, K's move no score by more than 2^-33), walks
+// its half tiles once more on the fp32 matrix instructions
+// (v_mfma_f32_32x32x2_f32) and the values as they are. So do walks over
+// infinite or NaN inputs. Weights below 2^-102 of the largest keep an absolute
+// 2^-126 of it.
 //
 // A workgroup of four waves owns one (head, 64-query block) or one key range
 // of it. Wave w walks the half tiles w, w + 4, ... of the list with its own
@@ -1159,57 +1161,39 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(const float* __restrict_
 // bound. A lane's V column (the A operand of O^T = V^T P^T) is contiguous
 // across lanes as it stands and goes straight to registers.
 //
-// Bound by VALU issue beside the matrix cores (a half tile: 48 matrix
-// instructions, 1536 cycles, and 380 VALU ones, most of them the splits of K
-// and V) and, through the clock, by power. Every head dense at 10992 tokens,
-// 16 heads: 5.14 ms (96 TFLOP/s) with one wave per item on the fp32 matrix
-// instructions, 1.72 ms (288 TFLOP/s) so; relative error against 64 bits
-// 8e-7 before, 4e-7 now.
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-
-// Shared exponents as biased fp32 exponents of the largest value, kept where
-// the scale 2^(136 - e) and its inverse are normal; a largest value of 0 gives
-// that of 1.
-constexpr float kHeadroom = 8.f;
-__device__ inline int biased_exp(float x) { return x == 0.f ? 127 : max((int)((__float_as_uint(x) >> 23) & 255u), 15); }
-__device__ inline float exp_scale(int e) { return __uint_as_float((uint32_t)(263 - e) << 23); }
-__device__ inline float exp_unscale(int e) { return __uint_as_float((uint32_t)(e - 9) << 23); }
-
-struct SplitF16 {
-  f16x8 hi, lo;
+// Bound by the matrix cores (a half tile: 96 matrix instructions, 3072 cycles)
+// beside VALU issue (most of it the splits of K, V and P). Every head dense at
+// 10992 tokens, 16 heads: 5.02 ms (99 TFLOP/s) with one wave per item on the
+// fp32 matrix instructions, 2.45 ms (202 TFLOP/s) so, relative error against 64
+// bits 1.5e-6 before, 4.9e-7 now; with every walk made twice, 5.7 ms. (Pairs of
+// scaled f16 values, three products, take 1.5 ms, but hold a value to an
+// absolute 2^-35 of the largest that shares its scale, and weights likewise.)
+struct SplitBf16 {
+  bf16x8 part[3];  // hi, mid, lo
 };
-// x[0..7] * scale as (hi, lo) pairs; the products and differences are exact.
-// Per pair of values two multiplies (kScaled), v_cvt_pk_f16_f32, two
-// v_fma_mix_f32 (which read the packed halves as they stand) and
-// v_cvt_pk_f16_f32; the empty asm keeps the compiler from converting each half
-// once more on its own, and without kScaled `scale` is a 1 that it cannot see.
-// (v_fma_mixlo_f16 / v_fma_mixhi_f16 would take four instructions instead of
-// six, but issue at the rate of an exponential: 7% slower.)
-template <bool kScaled>
-__device__ __forceinline__ SplitF16 split_f16(const float (&x)[8], float scale) {
-  SplitF16 r;
+// The empty asm keeps the compiler from converting each half of a packed pair
+// once more on its own.
+__device__ __forceinline__ SplitBf16 split_bf16(const float (&x)[8]) {
+  SplitBf16 r;
 #pragma unroll
   for (int e = 0; e < 8; e += 2) {
-    const f32x2 xs = kScaled ? f32x2{x[e] * scale, x[e + 1] * scale} : f32x2{x[e], x[e + 1]};
-    uint32_t hb = __builtin_bit_cast(uint32_t, __builtin_convertvector(xs, f16x2));
-    asm("" : "+v"(hb));
-    const f16x2 h = __builtin_bit_cast(f16x2, hb);
-    const f32x2 rest = {fmaf(x[e], scale, -(float)h[0]), fmaf(x[e + 1], scale, -(float)h[1])};
-    const f16x2 lo = __builtin_convertvector(rest, f16x2);
-    r.hi[e] = h[0];
-    r.hi[e + 1] = h[1];
-    r.lo[e] = lo[0];
-    r.lo[e + 1] = lo[1];
+    f32x2 rest = {x[e], x[e + 1]};
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      uint32_t b = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16x2));
+      asm("" : "+v"(b));
+      const bf16x2 y = __builtin_bit_cast(bf16x2, b);
+      r.part[t][e] = y[0];
+      r.part[t][e + 1] = y[1];
+      if (t < 2) rest = f32x2{rest[0] - __uint_as_float(b << 16), rest[1] - __uint_as_float(b & 0xffff0000u)};
+    }
   }
   return r;
 }
-
-__device__ inline float wave_max(float x) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) x = fmaxf(x, __shfl_xor(x, m));
-  return x;
-}
+// The six products by the parts of their factors, the smallest first.
+constexpr int kProducts = 6;
+constexpr int kPartA[kProducts] = {2, 0, 1, 1, 0, 0};
+constexpr int kPartB[kProducts] = {0, 2, 1, 0, 1, 0};
 
 // A descriptor over rows [tok, n) of a head of 256-byte fp32 rows (empty for tok outside [0, n)).
 __device__ inline __amdgpu_buffer_rsrc_t rows_from(const float* head, uint32_t tok, uint32_t n) {
@@ -1241,8 +1225,9 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, float* __restrict__ out,
     float* __restrict__ lse, AttnArgs a) {
-  // split Q^T in B-operand order: [hi, lo][dims 16s ..][query half][lane] 16 bytes
-  __shared__ __attribute__((aligned(16))) f16x8 qs[2][4][2][64];
+  // split Q^T in B-operand order: [hi, mid, lo][dims 16s ..][query half][lane] 16 bytes
+  __shared__ __attribute__((aligned(16))) bf16x8 qs[3][4][2][64];
+  __shared__ int q_odd[kF32Waves];  // a wave's part of Q leaves the split form's range
   // per wave a K half tile: 32 rows of 256 B, 16-byte chunk c of row r at slot
   // c ^ (r & 15), which spreads a chunk's reads over the banks
   __shared__ __attribute__((aligned(1024))) char kbuf[kF32Waves][32 * 256];
@@ -1274,33 +1259,32 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
   const float* const vh = v + head_off;
   const __amdgpu_buffer_rsrc_t rq = make_rsrc(q + head_off, head_bytes);
 
-  // Q: lane (l32, hf) takes dims 16s + 8hf .. of queries l32 and 32 + l32;
-  // every wave finds all the queries' exponents, and splits its own s
-  float scq[2];  // log2(e) / 8 times the query's unscale
-  float one = 1.0f;
-  asm("" : "+s"(one));
+  // Q: wave s splits dims 16s ..; lane (l32, hf) dims 16s + 8hf .. of queries l32 and 32 + l32
+  {
+    uint32_t large = 0, small = ~0u;  // largest and smallest nonzero magnitude, as bits << 1
 #pragma unroll
-  for (int tq = 0; tq < 2; ++tq) {
-    float own[8];
-    float mx = 0.f;
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
+    for (int tq = 0; tq < 2; ++tq) {
+      float x[8];
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         const f32x4 y = __builtin_bit_cast(
             f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                       rq, ((w.i * kBlock + 32 * tq + l32) * kHeadDim + 16 * s + 8 * hf + 4 * c) * 4, 0, 0));
+                       rq, ((w.i * kBlock + 32 * tq + l32) * kHeadDim + 16 * wave + 8 * hf + 4 * c) * 4, 0, 0));
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          mx = fmaxf(mx, fabsf(y[e]));
-          if (s == wave) own[4 * c + e] = y[e];
+          x[4 * c + e] = y[e];
+          const uint32_t mag = __float_as_uint(y[e]) << 1;
+          large = max(large, mag);
+          small = min(small, mag - 1);  // 0 wraps to the largest
         }
       }
-    const int eq = biased_exp(pair_max(mx));
-    scq[tq] = a.scale_log2 * exp_unscale(eq);
-    const SplitF16 p = split_f16<true>(own, exp_scale(eq));
-    qs[0][wave][tq][lane] = p.hi;
-    qs[1][wave][tq][lane] = p.lo;
+      const SplitBf16 p = split_bf16(x);
+#pragma unroll
+      for (int t = 0; t < 3; ++t) qs[t][wave][tq][lane] = p.part[t];
+    }
+    const bool odd = large >= (127u + 90) << 24 || small < ((127u - 100) << 24) - 1;
+    const bool any_odd = __ballot(odd) != 0;
+    if (lane == 0) q_odd[wave] = any_odd ? 1 : 0;
   }
 
   f32x16 o[2][2];
@@ -1310,9 +1294,10 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
     for (int tq = 0; tq < 2; ++tq)
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[c][tq][e] = 0.f;
-  float nm[2] = {-kNegInf, -kNegInf};  // kHeadroom minus the running max of the log2-scaled scores
+  float nm[2] = {-kNegInf, -kNegInf};  // minus the running max of the log2-scaled scores
   float l[2] = {0.f, 0.f};
   const bool tail = (nkeys % kBlock) != 0;
+  const float sc = a.scale_log2;
 
   // This wave's half tiles: half h = wave & 1 of list entries wave / 2, wave / 2 + 2, ...
   const int h = wave & 1;
@@ -1351,21 +1336,18 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
   // (a descriptor per u, so that the rest of an offset fits the instruction)
   // (each call's own copy, so that no sum of it is hoisted into a register)
   int v_off = 4 * hf * (kHeadDim * 4) + 4 * l32;
-  auto load_v = [&](int j, float (&x)[2][2][8]) {
+  auto load_v = [&](int j, int u, float (&x)[2][8]) {
     asm volatile("" : "+v"(v_off));
+    const __amdgpu_buffer_rsrc_t r = rows_from(vh, first_token(j) + 16 * u * stride, n);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const __amdgpu_buffer_rsrc_t r = rows_from(vh, first_token(j) + 16 * u * stride, n);
+    for (int e = 0; e < 8; ++e)
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-          x[u][c][e] = __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
-              r,
-              kMode == kStrided ? row_off(8 * (e >> 2) + (e & 3) + 4 * hf) + 4 * l32 + 128 * c
-                                : v_off + (8 * (e >> 2) + (e & 3)) * (kHeadDim * 4) + 128 * c,
-              0, 0));
-    }
+      for (int c = 0; c < 2; ++c)
+        x[c][e] = __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
+            r,
+            kMode == kStrided ? row_off(8 * (e >> 2) + (e & 3) + 4 * hf) + 4 * l32 + 128 * c
+                              : v_off + (8 * (e >> 2) + (e & 3)) * (kHeadDim * 4) + 128 * c,
+            0, 0));
   };
 
   float vx[2][2][8];
@@ -1375,9 +1357,11 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
     j = block_at(it);
     jn = block_at(it + 2);
     load_k(j);
-    load_v(j, vx);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) load_v(j, u, vx[u]);
   }
   __syncthreads();  // Q's parts of all waves
+  const bool odd = __builtin_amdgcn_readfirstlane(q_odd[0] | q_odd[1] | q_odd[2] | q_odd[3]) != 0;
   // K of this step from LDS: row l32, dims 16s + 8hf + (0..7). Its loads have
   // landed when only the 32 V loads issued after them are in flight.
   auto read_k = [&](float (&x)[4][8]) {
@@ -1391,33 +1375,13 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
         for (int e = 0; e < 4; ++e) x[s][4 * c + e] = y[e];
       }
   };
-  float k_scale = 1.f, v_scale = 1.f, v_unscale = 1.f;
-  float sc[2] = {scq[0], scq[1]};
-  if (it < count) {
-    float kx[4][8], mk = 0.f, mv = 0.f;
-    read_k(kx);
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        mk = fmaxf(mk, fabsf(kx[s][e]));
-        mv = fmaxf(mv, fabsf(vx[s >> 1][s & 1][e]));
-      }
-    const int ek = __builtin_amdgcn_readfirstlane(biased_exp(wave_max(mk)));
-    const int ev = __builtin_amdgcn_readfirstlane(biased_exp(wave_max(mv)));
-    k_scale = exp_scale(ek);
-    v_scale = exp_scale(ev);
-    v_unscale = exp_unscale(ev);
-    sc[0] *= exp_unscale(ek);
-    sc[1] *= exp_unscale(ek);
-  }
-  f16x8 qh[2][4];
+  bf16x8 qh[2][4];
 #pragma unroll
   for (int s = 0; s < 4; ++s)
 #pragma unroll
     for (int tq = 0; tq < 2; ++tq) qh[tq][s] = qs[0][s][tq][lane];
   int q_pos = lane;
-  for (; it < count; it += 2) {
+  for (; it < count && !odd; it += 2) {
     const int j2 = block_at(it + 4);
     // ---- S^T = K Q^T
     f32x16 s_acc[2] = {};
@@ -1426,24 +1390,29 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
       read_k(kx);
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read: the buffer may be filled again
       load_k(jn);
-      SplitF16 kp[4];
-#pragma unroll
-      for (int s = 0; s < 4; ++s) kp[s] = split_f16<true>(kx[s], k_scale);
+      // the small products of all 64 dims first: the sum then rounds at its
+      // full size in the four hi hi instructions alone
+      bf16x8 kh[4];
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        // read again in every half tile: hoisted, it would take 32 registers more
+        const SplitBf16 kp = split_bf16(kx[s]);
+        kh[s] = kp.part[0];
+        // read again in every half tile: hoisted, they would take 64 registers more
         asm volatile("" : "+v"(q_pos));
-        const f16x8 ql[2] = {qs[1][s][0][q_pos], qs[1][s][1][q_pos]};
+        const bf16x8 qp[3][2] = {{qh[0][s], qh[1][s]},
+                                 {qs[1][s][0][q_pos], qs[1][s][1][q_pos]},
+                                 {qs[2][s][0][q_pos], qs[2][s][1][q_pos]}};
 #pragma unroll
-        for (int tq = 0; tq < 2; ++tq)
-          s_acc[tq] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kp[s].lo, qh[tq][s], s_acc[tq], 0, 0, 0);
+        for (int t = 0; t + 1 < kProducts; ++t)
 #pragma unroll
-        for (int tq = 0; tq < 2; ++tq)
-          s_acc[tq] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kp[s].hi, ql[tq], s_acc[tq], 0, 0, 0);
-#pragma unroll
-        for (int tq = 0; tq < 2; ++tq)
-          s_acc[tq] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kp[s].hi, qh[tq][s], s_acc[tq], 0, 0, 0);
+          for (int tq = 0; tq < 2; ++tq)
+            s_acc[tq] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kp.part[kPartA[t]], qp[kPartB[t]][tq], s_acc[tq], 0, 0, 0);
       }
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int tq = 0; tq < 2; ++tq)
+          s_acc[tq] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh[s], qh[tq][s], s_acc[tq], 0, 0, 0);
     }
     float add[2] = {nm[0], nm[1]};
     if (tail && j == last_block) {
@@ -1459,33 +1428,28 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
     }
 
     // ---- online softmax
-    SplitF16 p[2][2];
+    float p[2][2][8];
     float rs[2];
     auto probs = [&]() {
 #pragma unroll
       for (int tq = 0; tq < 2; ++tq) {
         rs[tq] = 0.f;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          float pe[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            pe[e] = fast_exp2(fmaf(s_acc[tq][8 * u + e], sc[tq], add[tq]));
-            rs[tq] += pe[e];
-          }
-          p[u][tq] = split_f16<false>(pe, one);
+        for (int e = 0; e < 16; ++e) {
+          p[e >> 3][tq][e & 7] = fast_exp2(fmaf(s_acc[tq][e], sc, add[tq]));
+          rs[tq] += p[e >> 3][tq][e & 7];
         }
       }
     };
     probs();
-    // a lane's share above 2^15 (as unsigned bits, so also inf and NaN): the max moves
-    if (__ballot(__float_as_uint(rs[0]) > 0x47000000u || __float_as_uint(rs[1]) > 0x47000000u)) {
+    // a lane's share above 2^12 (as unsigned bits, so also inf and NaN): the max moves
+    if (__ballot(__float_as_uint(rs[0]) > 0x45800000u || __float_as_uint(rs[1]) > 0x45800000u)) {
 #pragma unroll
       for (int tq = 0; tq < 2; ++tq) {
         float mx = s_acc[tq][0];
 #pragma unroll
         for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s_acc[tq][e]);
-        const float nmnew = fminf(kHeadroom - pair_max(mx) * sc[tq], nm[tq]);
+        const float nmnew = fminf(-(pair_max(mx) * sc), nm[tq]);
         const float alpha = fast_exp2(nmnew - nm[tq]);
         nm[tq] = add[tq] = nmnew;
         l[tq] *= alpha;
@@ -1498,43 +1462,41 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
     l[1] += rs[1];
 
     // ---- O^T += V^T P^T
-    SplitF16 vp[2][2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int c = 0; c < 2; ++c) vp[u][c] = split_f16<true>(vx[u][c], v_scale);
-    load_v(jn, vx);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
+      const SplitBf16 vp[2] = {split_bf16(vx[u][0]), split_bf16(vx[u][1])};
+      load_v(jn, u, vx[u]);
+      const SplitBf16 pp[2] = {split_bf16(p[u][0]), split_bf16(p[u][1])};
 #pragma unroll
-      for (int c = 0; c < 2; ++c)
+      for (int t = 0; t < kProducts; ++t)
 #pragma unroll
-        for (int tq = 0; tq < 2; ++tq)
-          o[c][tq] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vp[u][c].lo, p[u][tq].hi, o[c][tq], 0, 0, 0);
+        for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int tq = 0; tq < 2; ++tq)
-          o[c][tq] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vp[u][c].hi, p[u][tq].lo, o[c][tq], 0, 0, 0);
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int tq = 0; tq < 2; ++tq)
-          o[c][tq] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vp[u][c].hi, p[u][tq].hi, o[c][tq], 0, 0, 0);
+          for (int tq = 0; tq < 2; ++tq)
+            o[c][tq] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vp[c].part[kPartA[t]], pp[tq].part[kPartB[t]], o[c][tq],
+                                                               0, 0, 0);
     }
     j = jn;
     jn = j2;
   }
 
-  // ---- not finite (see above): once more on the fp32 matrix instructions
+  // ---- outside the split form (see above): once more on the fp32 matrix instructions
   float bad = l[0] * 0.f + l[1] * 0.f;
+  uint32_t small[2] = {~0u, ~0u};  // smallest nonzero |O| of the lane's queries, as bits << 1, less 1
 #pragma unroll
   for (int c = 0; c < 2; ++c)
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) bad = fmaf(o[c][t][e], 0.f, bad);
-  if (__ballot(bad != 0.f)) {
+      for (int e = 0; e < 16; ++e) {
+        bad = fmaf(o[c][t][e], 0.f, bad);
+        small[t] = min(small[t], (__float_as_uint(o[c][t][e]) << 1) - 1);
+      }
+  bool again = odd || bad != 0.f;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)  // |O| / l < 2^-100, l the whole row sum of this wave
+    again = again || small[t] < __float_as_uint(pair_sum(l[t]) * 0x1p-100f) << 1;
+  if (__ballot(again)) {
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
 #pragma unroll
     for (int c = 0; c < 2; ++c)
@@ -1542,7 +1504,6 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
       for (int t = 0; t < 2; ++t) o[c][t] = f32x16{};
     float m[2] = {kNegInf, kNegInf};
     l[0] = l[1] = 0.f;
-    v_unscale = 1.f;
     for (it = wave >> 1; it < count; it += 2) {
       j = block_at(it);
       const int valid = min(nkeys - j * kBlock - 32 * h, 32);
@@ -1562,7 +1523,8 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
           s_acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(hf ? x[3] : x[2], hf ? y[3] : y[2], s_acc[t], 0, 0, 0);
         }
       }
-      load_v(j, vx);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) load_v(j, u, vx[u]);
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         float mx = kNegInf;
@@ -1571,7 +1533,7 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
           if (j == last_block && 8 * (e >> 2) + 4 * hf + (e & 3) >= valid) s_acc[t][e] = kNegInf;
           mx = fmaxf(mx, s_acc[t][e]);
         }
-        const float mnew = fmaxf(m[t], pair_max(mx) * a.scale_log2);
+        const float mnew = fmaxf(m[t], pair_max(mx) * sc);
         const float alpha = fast_exp2(m[t] - mnew);
         m[t] = mnew;
         l[t] *= alpha;
@@ -1579,7 +1541,7 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
         for (int c = 0; c < 2; ++c) o[c][t] *= alpha;
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          s_acc[t][e] = fast_exp2(fmaf(s_acc[t][e], a.scale_log2, -mnew));
+          s_acc[t][e] = fast_exp2(fmaf(s_acc[t][e], sc, -mnew));
           l[t] += s_acc[t][e];
         }
       }
@@ -1596,22 +1558,20 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
     nm[1] = -m[1];
   }
 
-  // ---- the four waves' parts: weights 2^(m_w - M) 2^(e_w) on O^T, through LDS
-  // (running max, row sum, unscale) per wave and query into Q's array, O^T in
-  // two rounds (head-dim halves) into the K buffers, 8 KB a wave
+  // ---- the four waves' parts: weights 2^(m_w - M) on O^T, through LDS:
+  // (running max, row sum) per wave and query into Q's array, O^T in two
+  // rounds (head-dim halves) into the K buffers, 8 KB a wave
   const float lt[2] = {pair_sum(l[0]), pair_sum(l[1])};
   __builtin_amdgcn_s_waitcnt(kWaitVm0);  // the last prefetch into the K buffer
   __syncthreads();                       // every wave is done with Q
   f32x2* const ml = (f32x2*)qs;          // [wave][64] (max, sum)
-  float* const vun = (float*)(ml + kF32Waves * 64);
   if (hf == 0) {
 #pragma unroll
     for (int tq = 0; tq < 2; ++tq) ml[wave * 64 + 32 * tq + l32] = f32x2{-nm[tq], lt[tq]};
   }
-  if (lane == 0) vun[wave] = v_unscale;
   // this wave sums query half tq, 16-byte groups g2, g2 + 1 of the registers
   const int tq = wave & 1, g2 = 2 * (wave >> 1);
-  float m = kNegInf, sum = 0.f, f[kF32Waves];
+  float m = kNegInf, sum = 0.f, inv = 1.0f, f[kF32Waves];
   const int query = w.i * kBlock + 32 * tq + l32;
   const __amdgpu_buffer_rsrc_t ro = make_rsrc(out + head_off, head_bytes);
 #pragma unroll
@@ -1633,15 +1593,12 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
       }
 #pragma unroll
       for (int u = 0; u < kF32Waves; ++u) {
-        const float wgt = x[u][0] == kNegInf ? 0.f : fast_exp2(x[u][0] - m);
-        sum = fmaf(wgt, x[u][1], sum);
-        f[u] = wgt * vun[u];
+        f[u] = x[u][0] == kNegInf ? 0.f : fast_exp2(x[u][0] - m);
+        sum = fmaf(f[u], x[u][1], sum);
       }
       const bool part = kMode == kLists && w.chunk >= 0;  // a split item: the merge combines the ranges
       // an empty list (no keys) gives a zero output and LSE -inf
-      const float inv = part ? 1.0f : sum > 0.f ? 1.0f / sum : 0.f;
-#pragma unroll
-      for (int u = 0; u < kF32Waves; ++u) f[u] *= inv;
+      if (!part) inv = sum > 0.f ? 1.0f / sum : 0.f;
       if (g2 == 0 && hf == 0) {
         if (part)
           *(f32x2*)(a.part_ml + ((int64_t)w.item * kBlock + 32 * tq + l32) * 2) = f32x2{m, sum};
@@ -1661,7 +1618,7 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
       if (kMode == kLists && w.chunk >= 0)
         *(f32x4*)(a.part_o + (int64_t)w.item * (kBlock * kHeadDim) + (((c * 2 + tq) * 4 + g) * 64 + lane) * 4) = ov;
       else
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, ov), ro,
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, ov * inv), ro,
                                                (query * kHeadDim + 32 * c + 8 * g + 4 * hf) * 4, 0, 0);
     }
   }

@@ -529,22 +529,31 @@ def _fp32_layer(frames, tpf, seed, change):
     change(q, k, v)
     table = [(O.DENSE, 0), (O.FRAME_LOCAL, 0), (O.STRIDE, max(1, min(w.tokens, w.tokens // 9)))]
     ref = O.run_layer(q, k, v, table, tpf, "f32")
-    return w, v, table, ref, [PT.gpu_layer(P, w, q, k, v, table, workspace=ws) for ws in (False, True)]
+    return w, q, k, v, table, ref, [PT.gpu_layer(P, w, q, k, v, table, workspace=ws) for ws in (False, True)]
 
 
 # N = 65 and 97: a last block whose second half holds no key at all; 8 and 40 tokens: one half tile, and waves without
 # any; 4500: a dense row of 71 blocks that the workspace splits into key ranges
 @pytest.mark.parametrize("frames,tpf", [(1, 8), (1, 40), (1, 65), (1, 97), (2, 161), (3, 300), (1, 4500)])
-@pytest.mark.parametrize("scales", ["plain", "late", "tiny", "first"])
+@pytest.mark.parametrize("scales", ["plain", "late", "tiny", "first", "zero first", "zero first, far below", "dimensions",
+                                    "dominant", "channel", "large queries"])
 def test_fp32_value_ranges(gpu_lib, frames, tpf, scales):
-    """fp32 operands run as scaled f16 pairs: the error bound of plain inputs
-    holds, times the largest |V|, where the values' size changes along the
-    keys (past what the first tile's scale covers), is far below 1, or falls
-    by 1000 after the first block."""
+    """fp32 accuracy in every output by itself, whatever the values' sizes:
+    sizes that change along the keys, far below 1, 0 in the first blocks, other
+    ones from dimension to dimension; a key that takes nearly all the weight
+    and has no value; a channel of K that Q does not use.
+
+    The bound of output (query i, dimension d), with u = 2^-24: its weighted
+    sum of |V|, A_id, times the relative error of the weights and of the sum. A
+    score's 64 products of total size Z_i (at most) are summed and scaled in
+    fp32 in parts of at most 32 terms: off by 5 u Z_i at most in practice, once
+    in the weight and once in the normaliser; exponentials and the sum over the
+    keys, in parts, add 32 u. Every term is relative to A_id: no other
+    dimension, query or key enters."""
     def change(q, k, v):
         half = k.shape[1] // 2
         if scales == "late":
-            k[:, half:half + 3] *= np.float32(30)  # times the special keys' 4 and Q: leaves f16 at the first tile's scale
+            k[:, half:half + 3] *= np.float32(30)
             q *= np.float32(0.02)
             v[:, half:half + 3] *= np.float32(1e5)
         elif scales == "tiny":
@@ -553,12 +562,45 @@ def test_fp32_value_ranges(gpu_lib, frames, tpf, scales):
             v *= np.float32(1e-30)
         elif scales == "first":
             v[:, 64:] *= np.float32(1e-3)
+        elif scales.startswith("zero first"):
+            q *= np.float32(0.1)
+            v *= np.float32(1e-24 if scales.endswith("below") else 1e-8)
+            v[:, :128] = 0
+        elif scales == "dimensions":
+            q *= np.float32(0.1)
+            v[:, :, 5] *= np.float32(1e-7)
+            v[:, :, 9] *= np.float32(1e-20)
+            v[:, :, 40] *= np.float32(1e-33)
+            v[:, :, 63] = 0
+        elif scales == "dominant":  # 25 nats above the others at scores of about 1
+            q *= np.float32(0.1)
+            q[:, :, 0] = 4
+            k[:, :, 0] = 0
+            k[:, half] = 0
+            k[:, half, 0] = 50
+            v[:, half] = 0
+        elif scales == "channel":
+            q *= np.float32(0.1)
+            q[:, :, 3] = 0
+            k[:, :, 3] *= np.float32(1e6)
+        elif scales == "large queries":
+            q *= np.float32(1e28)
+            k *= np.float32(1e-28)
 
-    w, v, table, ref, results = _fp32_layer(frames, tpf, 5, change)
-    for res in results:
-        for h in range(3):
-            assert PT.max_abs(res["out"][h], ref["out"][h]) <= PT.TOL_F32 * max(1e-30, float(np.abs(v[h]).max())), h
+    w, q, k, v, table, ref, results = _fp32_layer(frames, tpf, 5, change)
+    size = O.run_layer(q, k, np.abs(v), table, tpf, "f32")["out"]
+    u = 2.0 ** -24
+    worst = 0.0
+    for h in range(3):
+        z = (np.abs(q[h].astype(np.float64)) @ np.abs(k[h].astype(np.float64)).T).max(axis=1) / 8
+        bound = u * (10 * z[:, None] + 32) * size[h]
+        for res in results:
+            err = np.abs(res["out"][h] - ref["out"][h])
+            over = err - bound
+            worst = max(worst, float(np.max(err / np.where(bound > 0, bound, 1.0))))
+            assert np.all(over <= 0), (h, np.unravel_index(np.argmax(over), over.shape), worst)
             assert PT.max_abs(res["lse"][h], ref["lse"][h]) <= PT.LSE_TOL_F32, h
+    print(f"[parity] fp32 {scales} {frames}x{tpf}: at most {worst:.3f} of the bound", flush=True)
 
 
 @pytest.mark.parametrize("tensor,value", [("k", np.nan), ("k", np.inf), ("v", np.nan), ("v", np.inf), ("v", -np.inf)])
@@ -572,7 +614,7 @@ def test_fp32_infinities_and_nans_stay_where_they_belong(gpu_lib, tensor, value)
         {"k": k, "v": v}[tensor][:, tok, dim] = value
 
     with np.errstate(all="ignore"):
-        w, v, table, ref, results = _fp32_layer(3, 300, 9, change)
+        w, q, k, v, table, ref, results = _fp32_layer(3, 300, 9, change)
     for res in results:
         for h in range(3):
             got, want = res["out"][h], ref["out"][h]
