@@ -304,7 +304,9 @@ int64_t saf3r_cosine_workspace_bytes(const saf3r_problem* problem, int32_t feat_
  * depend on the features only: the paper computes them once per sequence
  * and reuses them in every layer, and saf3r_select_blocks leaves these rows
  * untouched so a caller can do the same.
- *   features         device [N, feat_dim] of problem->dtype; every row non-zero
+ *   features         device [N, feat_dim] of problem->dtype; a block with a
+ *                    zero, infinite or NaN row ranks last in its frame, and
+ *                    such a query block keeps every frame's first blocks
  *   feat_dim         1 .. 4096
  *   workspace        device, >= saf3r_cosine_workspace_bytes bytes, 8-byte
  *                    aligned; overwritten (block features, similarity matrix)

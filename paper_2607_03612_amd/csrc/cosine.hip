@@ -361,7 +361,8 @@ __global__ __launch_bounds__(256) void cosine_sim_mfma_kernel(const double* __re
       for (int e = 0; e < 4; ++e) {
         const int row = r0 + 16 * x + sub + 4 * e;
         const int col = c0 + 16 * y + (lane & 15);
-        const double v = acc[x][y][e] + sums[wave & 1][(2 * x + y) * 4 + e][lane];
+        // NaN (of a zero, infinite or NaN feature row) ranks last, so that the lists can order every pair
+        const double v = fmax(acc[x][y][e] + sums[wave & 1][(2 * x + y) * 4 + e][lane], -__builtin_inf());
         if (row <= col && col < nb) {
           sim[(int64_t)row * nb + col] = v;
           sim[(int64_t)col * nb + row] = v;
@@ -386,7 +387,8 @@ __device__ inline int lane_scan_incl(int v) {
 
 // The kFew best (value desc, index asc) of row[j_lo, j_hi), best first; nb and
 // -inf where there are fewer. Indices ascend, so an equal value never ranks
-// before an earlier one and a pair moves up on a strictly larger value only.
+// before an earlier one and a pair moves up on a strictly larger value or into
+// an empty place only (a value may be -inf).
 template <int kFew>
 __device__ __forceinline__ void best_few(const double* row, int j_lo, int j_hi, int nb, double (&bv)[kFew],
                                          int (&bj)[kFew]) {
@@ -399,7 +401,7 @@ __device__ __forceinline__ void best_few(const double* row, int j_lo, int j_hi, 
     const double v = row[j];
     bool up[kFew];
 #pragma unroll
-    for (int p = 0; p < kFew; ++p) up[p] = v > bv[p];
+    for (int p = 0; p < kFew; ++p) up[p] = v > bv[p] || bj[p] == nb;
 #pragma unroll
     for (int p = kFew - 1; p >= 0; --p) {
       const bool shift = p > 0 && up[p > 0 ? p - 1 : 0];  // the pair before moves down to p

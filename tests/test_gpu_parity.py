@@ -1031,6 +1031,43 @@ def test_cosine_lists_many_frames(gpu_lib, frames, T, ks):
                            w.nb, cap, rank=_rank(O.COSINE_TOPK, table[h][1], ref["scores"][h], i, T))
 
 
+@pytest.mark.parametrize("dtype,dim", [("f32", 16), ("bf16", 64), ("f32", 7)])
+@pytest.mark.parametrize("ks", [(1, 2), (3, 4), (5, 64)])
+def test_cosine_lists_over_rows_without_a_direction(gpu_lib, dtype, dim, ks):
+    """Zero, infinite and NaN feature rows, whose similarities are NaN: their
+    blocks rank last in the frame, the lists keep their counts, order and
+    range, and no better block is displaced. Frame 2 has no other block."""
+    import torch
+
+    import paper_2607_03612_amd as P
+
+    frames, T = 6, 330
+    w = Workload(f"cosn-{dim}", frames, T, "f32", ("fixed", 1, 1, 50), heads=2)
+    f = _features(w.tokens, dim, frames, T, seed=dim)
+    f[5] = 0          # block 0
+    f[400, 1] = np.inf  # block 6
+    f[500, 0] = np.nan  # block 7
+    f[704:990:64] = 0  # blocks 11 .. 15, all of frame 2
+    f[w.tokens - 1] = 0  # the last block
+    t = torch.from_numpy(f).cuda().to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    table = [(O.COSINE_TOPK, x) for x in ks]
+    cap = P.index_capacity(table, frames, T, P.BF16)
+    idx = torch.full((2, w.nb, cap), -7, dtype=torch.int32, device="cuda")
+    cnt = torch.full((2, w.nb), -9, dtype=torch.int32, device="cuda")
+    P.cosine_select(t, table, frames, T, idx, cnt)
+    res = {"idx": idx.cpu().numpy(), "cnt": cnt.cpu().numpy()}
+    with np.errstate(all="ignore"):
+        fb = O.cosine_block_features(t.double().cpu().numpy(), 64)
+        sim = fb @ fb.T
+        bad = np.isnan(sim).all(axis=1)
+        assert list(np.nonzero(bad)[0]) == [0, 6, 7, 11, 12, 13, 14, 15, w.nb - 1]
+        for h, k in enumerate(ks):
+            for i in range(w.nb):
+                lst, margin = O.cosine_topk_row(sim[i], k, T, 64)
+                PT.check_lists(res, h, i, O.COSINE_TOPK, lst, np.inf if np.isnan(margin) else margin, w.nb, cap,
+                               rank=PT.ranking(O.COSINE_TOPK, k, sim[i], T))
+
+
 # widths: one, two and four 16-byte vectors per lane and row, more (rows read twice), no whole vectors, and a last run
 # of 8 dimensions that is shorter (even and odd); blocks: one, whole groups of 16 and one past them, two column bands;
 # k: each scan's form; 300 frames take two passes
