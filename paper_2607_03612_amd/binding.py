@@ -145,6 +145,20 @@ def _stream(stream):
     return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
+def _keep_until_done(stream, *temporaries):
+    """Memory of tensors that end with the call: not handed out again before
+    `stream`, where it is not the one they were allocated on, has run what the
+    call enqueued."""
+    import torch
+
+    if stream is None:
+        return
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream)
+    for t in temporaries:
+        t.record_stream(stream)
+
+
 def _check(status: int, where: str):
     if status != 0:
         raise Saf3rError(status, where)
@@ -297,6 +311,7 @@ def cosine_select(features, table, frames, tokens_per_frame, block_idx, block_cn
     nbytes = cosine_workspace_bytes(frames, tokens_per_frame, D, H, code)
     if workspace is None:
         workspace = torch.empty(nbytes // 8, dtype=torch.float64, device=features.device)
+        _keep_until_done(stream, workspace)
     p = problem(H, frames, tokens_per_frame, code)
     _check(_lib().saf3r_cosine_select(ctypes.byref(p), head_table(table), _ptr(features), int(D),
                                       _ptr(workspace), int(workspace.numel() * workspace.element_size()),
@@ -325,6 +340,7 @@ def nmse(o_full, o_sparse, frames, tokens_per_frame, out=None, workspace=None, s
     need = nmse_workspace_bytes(H, frames, tokens_per_frame, dtype)
     if workspace is None:
         workspace = torch.empty(need // 8, dtype=torch.float64, device=o_full.device)
+        _keep_until_done(stream, workspace)
     p = problem(H, frames, tokens_per_frame, dtype)
     _check(_lib().saf3r_nmse(ctypes.byref(p), _ptr(o_full), _ptr(o_sparse), _ptr(workspace),
                              ctypes.c_int64(workspace.numel() * workspace.element_size()),
@@ -379,6 +395,7 @@ def run_layer(q, k, v, table, frames, tokens_per_frame, stream=None):
     # the pooled arrays stay in here, and only the heads that are pooled are read: no need to clear them
     qp = torch.empty((H, nb, HEAD_DIM), dtype=torch.float64, device=q.device)
     kp = torch.empty((H, HEAD_DIM, nb), dtype=torch.float64, device=q.device)
+    _keep_until_done(stream, qp, kp)
     estimate_blocks(q, k, table, frames, tokens_per_frame, qp, kp, stream=stream)
     idx, cnt, _ = select_blocks(qp, kp, table, frames, tokens_per_frame, dtype=dtype, stream=stream)
     out, _ = sparse_attention(q, k, v, table, frames, tokens_per_frame, idx, cnt, stream=stream)

@@ -1229,6 +1229,44 @@ def test_skip_heads_split_a_layer_across_streams(gpu_lib):
 # ------------------------------------------- bounds of the tile loads
 
 
+def test_temporaries_outlive_the_stream_that_reads_them(gpu_lib):
+    """Calls on another stream, which is still busy when they return: what the
+    current stream allocates and writes then must not be the memory of the
+    calls' own temporaries (pooled arrays, workspaces)."""
+    import torch
+
+    import paper_2607_03612_amd as P
+
+    w = Workload("side", 4, 1374, "bf16", ("fixed", 1, 1, 25), heads=4)
+    q, k, v = (PT.to_device(x, "bf16") for x in make_qkv(w, seed=3))
+    table = [(P.TOPK, 9), (P.FRAME_LOCAL, 0), (P.TOPK, 5), (P.GLOBAL_PROBE, 7)]
+    cos = [(P.COSINE_TOPK, 2)] * 4
+    f = PT.to_device(_features(w.tokens, 64, 4, 1374, seed=2), "f32")
+    cap = P.index_capacity(cos, 4, 1374, P.F32)
+    lists = [(torch.zeros((4, w.nb, cap), dtype=torch.int32, device="cuda"),
+              torch.zeros((4, w.nb), dtype=torch.int32, device="cuda")) for _ in range(2)]
+    want = P.run_layer(q, k, v, table, 4, 1374)
+    P.cosine_select(f, cos, 4, 1374, *lists[0])
+    want_err = P.nmse(q, k, 4, 1374)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    side = torch.cuda.Stream()
+    err = torch.empty_like(want_err)
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(50_000_000)  # tens of milliseconds
+    got = P.run_layer(q, k, v, table, 4, 1374, stream=side)
+    P.cosine_select(f, cos, 4, 1374, *lists[1], stream=side)
+    P.nmse(q, k, 4, 1374, out=err, stream=side)
+    nan = [torch.full((n,), float("nan"), dtype=torch.float64, device="cuda")
+           for n in 2 * (4 * w.nb * 64, 4 * w.nb * 64, w.nb * (w.nb + 64),
+                         P.nmse_workspace_bytes(4, 4, 1374, P.BF16) // 8)]
+    torch.cuda.synchronize()
+    assert all(bool(x.isnan().all()) for x in nan)
+    for a, b in zip([*got, *lists[1], err], [*want, *lists[0], want_err]):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_rows_past_the_last_token_stay_unread_and_unwritten(gpu_lib, dtype):
     """A partial last key block (N = 10992 = 171 * 64 + 48) in the last head:
