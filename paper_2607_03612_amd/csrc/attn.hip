@@ -76,73 +76,6 @@ __device__ inline bf16x8 load_b128(__amdgpu_buffer_rsrc_t r, uint32_t byte_off) 
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-struct Work {
-  int h, i;
-  int chunk;  // key range of a split head's item, or -1
-  int item;   // split item index (partials), or -1
-  bool shared;  // bf16: the workgroup's waves share the row
-  bool valid;
-};
-
-// The last order position whose first unit start(pos) is at most u.
-template <typename Start>
-__device__ inline int order_position(const AttnArgs& a, int u, Start start) {
-  int lo = 0, hi = a.heads;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (start(mid) <= u) lo = mid;
-    else hi = mid;
-  }
-  return lo;
-}
-
-// Work unit u = b / 8 of order position hh covers unit_start[hh] <= u <
-// unit_start[hh + 1]: slab units per key range, key ranges in order, so the
-// items that run together on an XCD share one key range of one head.
-__device__ inline Work work_item(const AttnArgs& a) {
-  const int xcd = blockIdx.x & 7;
-  const int u = blockIdx.x >> 3;
-  Work w;
-  w.valid = u < a.unit_start[a.heads];
-  if (!w.valid) return w;
-  const int lo = order_position(a, u, [&](int p) { return a.unit_start[p]; });
-  const int r = u - a.unit_start[lo];
-  const int chunk = r / a.slab;
-  const int i = xcd * a.slab + (r - chunk * a.slab);
-  w.valid = i < a.nb;
-  w.h = a.order[lo];
-  w.i = i;
-  const int sp = a.split_pos[lo];
-  w.chunk = sp >= 0 ? chunk : -1;
-  w.item = sp >= 0 ? (sp * a.splits + chunk) * a.nb + i : -1;
-  return w;
-}
-
-// The same for workgroups of four waves (bf16): a unit is four neighbouring
-// query blocks, one a wave, or, for a head whose rows are shared, one query
-// block for all four. Slabs start one XCD further on from head to head, so
-// that the short last slab is not always the same XCD's.
-__device__ inline Work work_item4(const AttnArgs& a, int wave) {
-  const int u = blockIdx.x >> 3;
-  Work w;
-  w.valid = u < unit4_start(a, a.heads);
-  if (!w.valid) return w;
-  const int lo = order_position(a, u, [&](int p) { return unit4_start(a, p); });
-  w.shared = a.shared_before[lo + 1] > a.shared_before[lo];
-  const int slab = w.shared ? a.slab : a.slab4;
-  const int r = u - unit4_start(a, lo);
-  const int chunk = r / slab;
-  const int unit = (int)((blockIdx.x + lo) & 7) * slab + (r - chunk * slab);
-  const int i = w.shared ? unit : 4 * unit + wave;
-  w.valid = i < a.nb;
-  w.h = a.order[lo];
-  w.i = i;
-  const int sp = a.split_pos[lo];
-  w.chunk = sp >= 0 ? chunk : -1;
-  w.item = sp >= 0 ? (sp * a.splits + chunk) * a.nb + i : -1;
-  return w;
-}
-
 // A split item's share of its row: key blocks [c nb / splits, (c + 1) nb /
 // splits) of range c. A dense head's item walks every block of the range
 // (from dense_lo); a list head's item keeps its list's entries inside the
@@ -633,8 +566,8 @@ __device__ __forceinline__ void attn_bf16_items(const uint16_t* __restrict__ q, 
   const int wave = kWaves == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lds_off = wave * kHalfBytes;
   Work w;
-  if constexpr (kWaves == 1) w = work_item(a);
-  else w = work_item4(a, wave);
+  if constexpr (kWaves == 1) w = work_item(a, blockIdx.x);
+  else w = work_item4(a, blockIdx.x, wave);
   if (!w.valid) return;  // a wave on its own, or all four of a shared row
   const bool shared = kWaves > 1 && w.shared;
   // (not threadIdx.x & 63: with the mask the walk spills, and its matrix and
@@ -1232,7 +1165,7 @@ __global__ __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(
   // c ^ (r & 15), which spreads a chunk's reads over the banks
   __shared__ __attribute__((aligned(1024))) char kbuf[kF32Waves][32 * 256];
 
-  const Work w = work_item(a);
+  const Work w = work_item(a, blockIdx.x);
   if (!w.valid) return;  // the whole workgroup
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -147,6 +147,74 @@ __host__ __device__ inline int unit4_start(const AttnArgs& a, int pos) {
   return a.unit_start[pos] / a.slab * a.slab4 + a.shared_before[pos] * (a.slab - a.slab4);
 }
 
+// What workgroup `group` of an attention launch does.
+struct Work {
+  int h, i;
+  int chunk;  // key range of a split head's item, or -1
+  int item;   // split item index (partials), or -1
+  bool shared;  // bf16: the workgroup's waves share the row
+  bool valid;
+};
+
+// The last order position whose first unit start(pos) is at most u.
+template <typename Start>
+__host__ __device__ inline int order_position(const AttnArgs& a, int u, Start start) {
+  int lo = 0, hi = a.heads;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (start(mid) <= u) lo = mid;
+    else hi = mid;
+  }
+  return lo;
+}
+
+// Work unit u = b / 8 of order position hh covers unit_start[hh] <= u <
+// unit_start[hh + 1]: slab units per key range, key ranges in order, so the
+// items that run together on an XCD share one key range of one head.
+__host__ __device__ inline Work work_item(const AttnArgs& a, uint32_t group) {
+  const int xcd = group & 7;
+  const int u = group >> 3;
+  Work w;
+  w.valid = u < a.unit_start[a.heads];
+  if (!w.valid) return w;
+  const int lo = order_position(a, u, [&](int p) { return a.unit_start[p]; });
+  const int r = u - a.unit_start[lo];
+  const int chunk = r / a.slab;
+  const int i = xcd * a.slab + (r - chunk * a.slab);
+  w.valid = i < a.nb;
+  w.h = a.order[lo];
+  w.i = i;
+  const int sp = a.split_pos[lo];
+  w.chunk = sp >= 0 ? chunk : -1;
+  w.item = sp >= 0 ? (sp * a.splits + chunk) * a.nb + i : -1;
+  return w;
+}
+
+// The same for workgroups of four waves (bf16): a unit is four neighbouring
+// query blocks, one a wave, or, for a head whose rows are shared, one query
+// block for all four. Slabs start one XCD further on from head to head, so
+// that the short last slab is not always the same XCD's.
+__host__ __device__ inline Work work_item4(const AttnArgs& a, uint32_t group, int wave) {
+  const int u = group >> 3;
+  Work w;
+  w.valid = u < unit4_start(a, a.heads);
+  if (!w.valid) return w;
+  const int lo = order_position(a, u, [&](int p) { return unit4_start(a, p); });
+  w.shared = a.shared_before[lo + 1] > a.shared_before[lo];
+  const int slab = w.shared ? a.slab : a.slab4;
+  const int r = u - unit4_start(a, lo);
+  const int chunk = r / slab;
+  const int unit = (int)((group + lo) & 7) * slab + (r - chunk * slab);
+  const int i = w.shared ? unit : 4 * unit + wave;
+  w.valid = i < a.nb;
+  w.h = a.order[lo];
+  w.i = i;
+  const int sp = a.split_pos[lo];
+  w.chunk = sp >= 0 ? chunk : -1;
+  w.item = sp >= 0 ? (sp * a.splits + chunk) * a.nb + i : -1;
+  return w;
+}
+
 // The merge of split heads: one wave per (split head, query block).
 struct MergeArgs {
   int64_t n;

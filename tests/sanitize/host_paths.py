@@ -62,6 +62,29 @@ def test_valid_calls_reach_consistent_launches(heads, frames, T, table, dtype):
     assert lib.saf3r_nmse_noalloc(ctypes.byref(p), OK, OK, OK, None) == 0
 
 
+# rows that four waves share in bf16: beside short lists, in key ranges (with the workspace), strided, odd block counts
+@pytest.mark.parametrize("heads,frames,T,table", [
+    (4, 1, 520, [(B.DENSE, 0), (B.TOPK, 8), (B.TOPK, 1), (B.STRIDE, 1)]),
+    (5, 2, 1000, [(B.DENSE, 0), (B.TOPK, 31), (B.FRAME_LOCAL, 0), (B.ANCHOR, 1), (B.TOPK, 3)]),
+    (1, 1, 8300, [(B.DENSE, 0)]),
+    (16, 8, 1374, [(B.FRAME_LOCAL, 0)] * 6 + [(B.DENSE, 0)] + [(B.TOPK, 13)] * 9),
+    (3, 4, 1374, [(B.STRIDE, 3), (B.STRIDE, 500), (B.STRIDE, 11)]),
+    (12, 20, 1001, [(B.DENSE, 0)] * 3 + [(B.FRAME_LOCAL, 0)] * 4 + [(B.TOPK, 32)] * 5),
+])
+@pytest.mark.parametrize("workspace", [False, True])
+def test_shared_rows_reach_consistent_launches(heads, frames, T, table, workspace):
+    lib = B.load()
+    p = _p(heads, frames, T)
+    t = B.head_table(table)
+    cap = max(lib.saf3r_index_capacity(ctypes.byref(p), t), 1)
+    aws = lib.saf3r_attention_workspace_bytes(ctypes.byref(p), t)
+    launches = lib.saf3r_stub_attention_launches
+    before = launches(4)
+    assert lib.saf3r_sparse_attention(ctypes.byref(p), t, OK, OK, OK, OK, OK, cap, OK, OK,
+                                      OK if workspace else None, max(aws, 16) if workspace else 0, None) == 0
+    assert launches(4) > before
+
+
 def test_all_dense_table_is_one_launch():
     lib = B.load()
     p = _p(16, 100, 1374)

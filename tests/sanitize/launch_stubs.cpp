@@ -30,7 +30,48 @@ bool blocks_ok(int64_t n, int nb) { return n >= 1 && nb == (int)((n + kBlock - 1
 
 hipError_t launch_status(bool ok) { return ok ? hipSuccess : hipErrorInvalidValue; }
 
+int attention_launches[2] = {0, 0};  // of one wave and of four waves to a workgroup
+
+// The workgroups of a list or strided launch take every (head, key range,
+// query block) exactly once: one wave each, or all four waves of a workgroup
+// where the head's rows are shared. With the kernels' own work_item functions.
+bool covers_every_item(const AttnArgs& a) {
+  const bool four = a.waves == 4;
+  std::vector<int> pos_of(kMaxHeads, -1);
+  for (int p = 0; p < a.heads; ++p) pos_of[a.order[p]] = p;
+  std::vector<int> first(a.heads + 1, 0);  // of a head's items
+  for (int p = 0; p < a.heads; ++p) first[p + 1] = first[p] + a.nb * (a.split_pos[p] >= 0 ? a.splits : 1);
+  std::vector<int> taken(first[a.heads], 0);
+  const int groups = 8 * (four ? unit4_start(a, a.heads) : a.unit_start[a.heads]);
+  for (int g = 0; g < groups; ++g) {
+    int shared_item = -1;
+    for (int wave = 0; wave < a.waves; ++wave) {
+      const Work w = four ? work_item4(a, g, wave) : work_item(a, g);
+      if (!w.valid) continue;
+      const int p = w.h >= 0 && w.h < kMaxHeads ? pos_of[w.h] : -1;
+      if (p < 0 || w.i < 0 || w.i >= a.nb) return false;
+      const bool split = a.split_pos[p] >= 0;
+      if (split ? w.chunk < 0 || w.chunk >= a.splits : w.chunk != -1) return false;
+      if (w.item != (split ? (a.split_pos[p] * a.splits + w.chunk) * a.nb + w.i : -1)) return false;
+      const int item = first[p] + (split ? w.chunk : 0) * a.nb + w.i;
+      if (four && w.shared) {
+        if (wave > 0 && shared_item != item) return false;  // the four waves meet at barriers
+        if (wave == 0) ++taken[item];
+        shared_item = item;
+      } else {
+        if (shared_item >= 0) return false;
+        ++taken[item];
+      }
+    }
+  }
+  for (int t : taken)
+    if (t != 1) return false;
+  return true;
+}
+
 }  // namespace
+
+extern "C" int saf3r_stub_attention_launches(int waves) { return attention_launches[waves == 4 ? 1 : 0]; }
 
 hipError_t launch_pool(int dtype, const void* q, const void* k, double* qp, double* kp,
                        const PoolArgs& a, hipStream_t) {
@@ -100,13 +141,18 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
                             const int32_t*, const int32_t*, void* out, float*, const AttnArgs& a,
                             hipStream_t) {
   bool ok = (dtype == 0 || dtype == 1) && q && k && v && out && blocks_ok(a.n, a.nb) &&
-            a.slab == (a.nb + 7) / 8 && a.splits == kSplitChunks && a.mode >= 0 && a.mode <= 2 &&
-            heads_ok(a.order, a.heads, kMaxHeads) && a.unit_start[0] == 0;
+            a.slab == (a.nb + 7) / 8 && a.slab4 == ((a.nb + 3) / 4 + 7) / 8 && a.splits == kSplitChunks &&
+            a.mode >= 0 && a.mode <= 2 && (a.waves == 1 || (a.waves == 4 && dtype == 1 && a.mode != 1)) &&
+            heads_ok(a.order, a.heads, kMaxHeads) && a.unit_start[0] == 0 && a.shared_before[0] == 0;
+  bool any_shared = false;
   int n_split = 0;
   for (int i = 0; ok && i < a.heads; ++i) {
     const bool split = a.split_pos[i] >= 0;
     ok = a.unit_start[i + 1] == a.unit_start[i] + a.slab * (split ? a.splits : 1) &&
          a.split_pos[i] >= -1 && a.split_pos[i] < kMaxHeads && (!split || a.part_o);
+    const int shared = a.shared_before[i + 1] - a.shared_before[i];
+    ok = ok && (shared == 0 || (shared == (split ? a.splits : 1) && a.waves == 4));
+    any_shared = any_shared || shared != 0;
     if (split) {
       ok = ok && a.split_pos[i] == n_split && a.mode == 0;
       ++n_split;
@@ -116,6 +162,9 @@ hipError_t launch_attention(int dtype, const void* q, const void* k, const void*
   // the partials of split items start after the O accumulators
   if (ok && n_split > 0)
     ok = a.part_ml == a.part_o + (int64_t)n_split * a.splits * a.nb * kBlock * kHeadDim;
+  ok = ok && any_shared == (a.waves == 4);
+  if (ok && a.mode != 1) ok = covers_every_item(a);
+  if (ok && a.heads > 0) ++attention_launches[a.waves == 4 ? 1 : 0];
   return launch_status(ok);
 }
 

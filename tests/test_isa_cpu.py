@@ -71,9 +71,47 @@ def _kernel_body(text, substr):
 def test_sparse_attention_kernels_use_no_scratch(asm):
     # the list and strided walks fit in the registers of two waves per SIMD:
     # no spill stores or reloads anywhere in them
+    for kernel in ("attn_bf16_kernel", "attn_bf16_rows4_kernel", "attn_f32_kernel"):
+        for mode in ("ILi0E", "ILi2E"):
+            body = _kernel_body(asm["attn.hip"], kernel + mode)
+            assert "scratch_" not in body, (kernel, mode)
+
+
+def _fp32_walk_events(body):
+    """The tile loads of the fp32 walk in program order: D a buffer-to-LDS
+    load (K), V a 4-byte buffer load, W the walk's own wait for all but the
+    32 newest vector-memory operations (inline, not the compiler's)."""
+    events, asm_block = "", False
+    for line in body.splitlines():
+        x = line.strip()
+        if x.startswith(";;#ASMSTART") or x.startswith("; ASMSTART"):
+            asm_block = True
+        elif x.startswith(";;#ASMEND") or x.startswith("; ASMEND"):
+            asm_block = False
+        elif x.startswith("buffer_load") and " lds" in x:
+            events += "D"
+        elif re.match(r"buffer_load_dword\s", x):
+            events += "V"
+        elif asm_block and x == "s_waitcnt vmcnt(32)":
+            events += "W"
+    return events
+
+
+def test_fp32_walk_waits_for_its_k_tile(asm):
+    # K's eight buffer-to-LDS loads have landed when at most the 32 operations
+    # after them are in flight, so at least 32 V loads must follow them before
+    # the wait, both from the prologue into the loop and once round the loop
     for mode in ("ILi0E", "ILi2E"):
-        body = _kernel_body(asm["attn.hip"], "attn_bf16_kernel" + mode)
-        assert "scratch_" not in body, mode
+        events = _fp32_walk_events(_kernel_body(asm["attn.hip"], "attn_f32_kernel" + mode))
+        once = "D" * 8 + "V" * 32
+        assert events.startswith(once + "W" + once), (mode, events)
+        assert events.count("W") == 1 and events.count("D") == 16, (mode, events)
+
+
+def test_planted_missing_v_load_is_reported():
+    d, v = "\tbuffer_load_dwordx4 v1, s[0:3], 0 offen lds\n", "\tbuffer_load_dword v2, v1, s[0:3], 0 offen\n"
+    wait = "\t;;#ASMSTART\n\ts_waitcnt vmcnt(32)\n\t;;#ASMEND\n"
+    assert _fp32_walk_events(d * 8 + v * 31 + "\ts_waitcnt vmcnt(32)\n" + wait) == "D" * 8 + "V" * 31 + "W"
 
 
 def test_dense_kernel_loop_has_one_barrier_per_step_and_no_scratch(asm):
