@@ -170,12 +170,13 @@ saf3r_status saf3r_estimate_blocks(const saf3r_problem* problem, const saf3r_hea
  *                      matrix of every TOPK head; for a GLOBAL_PROBE head the
  *                      probe scores in row 0 (other rows and heads untouched)
  *   workspace_or_null  NULL: the TOPK rows are scored and selected in one
- *                      launch whose workgroups keep 16 score rows in LDS (the
- *                      library allocates nothing). Otherwise device memory,
- *                      16-byte aligned, of workspace_bytes bytes, overwritten:
- *                      above 256 blocks the TOPK scores go there as one
- *                      launch, and a second selects one row per wave at higher
- *                      occupancy (faster).
+ *                      launch whose workgroups keep 16 score rows in LDS, or 4
+ *                      on small layers (the library allocates nothing).
+ *                      Otherwise device memory, 16-byte aligned, of
+ *                      workspace_bytes bytes, overwritten: but for those small
+ *                      layers (up to 256 blocks and 512 groups of 4 TOPK rows)
+ *                      the TOPK scores go there as one launch, and a second
+ *                      selects one row per wave at higher occupancy (faster).
  *                      It must hold at least one TOPK head's share,
  *                      saf3r_select_workspace_bytes / (number of TOPK heads);
  *                      with less than the full size the heads are done in

@@ -243,7 +243,9 @@ saf3r_status saf3r_select_blocks(const saf3r_problem* problem, const saf3r_head_
   // one for each wave. With one: as many Top-K heads per pair of launches as
   // the workspace holds.
   constexpr size_t kLdsBudget = 150 * 1024;
-  int rows = s.nb <= saf3r::kOneLaunchBlocks ? 4 : 16;
+  const bool one_launch =
+      s.nb <= saf3r::kOneLaunchBlocks && (s.nb + 3) / 4 * ta.n_heads <= saf3r::kOneLaunchGroups;
+  int rows = one_launch ? 4 : 16;
   while (rows > 1 && saf3r::topk_lds_bytes(rows, s.nb) > kLdsBudget) rows /= 2;
   ta.rows_per_group = rows;
   const size_t lds = saf3r::topk_lds_bytes(rows, s.nb);
@@ -280,7 +282,7 @@ saf3r_status saf3r_select_blocks(const saf3r_problem* problem, const saf3r_head_
   if (e != hipSuccess) return SAF3R_ERR_HIP;
   e = saf3r::launch_select_global(q_pooled, k_pooled, block_idx, block_cnt, scores_or_null, ga, hs);
   if (e != hipSuccess) return SAF3R_ERR_HIP;
-  if (!workspace_or_null || s.nb <= saf3r::kOneLaunchBlocks)
+  if (!workspace_or_null || one_launch)
     return hip_status(saf3r::launch_select_topk(q_pooled, k_pooled, block_idx, block_cnt,
                                                 scores_or_null, ta, lds, hs));
   for (int b0 = 0; b0 < ta.n_heads; b0 += batch) {

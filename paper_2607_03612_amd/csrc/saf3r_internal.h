@@ -54,16 +54,23 @@ struct TopKArgs {
 };
 // Global-probe heads of layers up to this size go with the Top-K launch: their
 // one workgroup per head takes 6 KB + 12 bytes per block of LDS and writes
-// every row itself. 651 blocks, two such heads beside four Top-K heads: 35 us
-// for both instead of 37 + 5 and 17 one after the other.
+// every row itself. us for 4 Top-K heads and two such, with the Top-K launch /
+// in launches of their own: 9.7 / 23.1 at 128 blocks, 44.8 / 48.9 at 651, 61 / 67
+// at 900, 71 / 66 at 1024, 151 / 136 at 1700; beside 10 Top-K heads 85 / 105 at
+// 1024; without a workspace 52 / 55 at 1024.
 constexpr int kGlobalFusedBlocks = 1024;
-// Top-K rows of layers up to this size are scored and selected in one launch
-// with or without a workspace, four rows to a workgroup. Kernel time with the
-// static heads' rows, one launch / two and the static one: 17 blocks 7.9 / 15.2
-// us, 172 blocks 14.4 / 19.8; 651 blocks 61 / 51 (with a global-probe head 35),
-// 687 blocks 106 / 75. (Sixteen rows to a workgroup of 8 or 16 waves: 13 and 20
-// us at 17 blocks; two rows to one of two waves: 18 us at 172.)
+// Top-K rows of layers up to kOneLaunchBlocks are scored and selected in one
+// launch with or without a workspace, four rows to a workgroup, as long as that
+// makes at most two workgroups per CU: a third one's turn costs more than the
+// second launch (each workgroup reads every pooled key). us, one launch / two
+// (with a workspace): 10 Top-K heads beside 6 static ones 7.0 / 10.8 at 17
+// blocks, 13.8 / 15.4 at 172 (430 workgroups), 18.1 / 16.5 at 220 (550); 16
+// heads 12.2 / 14.3 at 128 (512), 16.8 / 15.7 at 172 (688), 27.6 / 18.8 at 256;
+// 40 heads 13.9 / 14.2 at 64 (640), 34.4 / 26.7 at 172. (Sixteen rows to a
+// workgroup of 8 or 16 waves: 13 and 20 us at 17 blocks; two rows to one of two
+// waves: 18 us at 172.)
 constexpr int kOneLaunchBlocks = 256;
+constexpr int kOneLaunchGroups = 512;
 
 struct StaticArgs {
   int64_t n;

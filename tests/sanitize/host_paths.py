@@ -62,6 +62,22 @@ def test_valid_calls_reach_consistent_launches(heads, frames, T, table, dtype):
     assert lib.saf3r_nmse_noalloc(ctypes.byref(p), OK, OK, OK, None) == 0
 
 
+# four rows to a workgroup, in one launch, up to 256 blocks and 512 workgroups
+@pytest.mark.parametrize("heads,nb,small", [(1, 17, True), (30, 65, True), (31, 65, False), (16, 128, True),
+                                            (17, 128, False), (8, 256, True), (9, 256, False), (16, 256, False),
+                                            (1, 257, False)])
+def test_small_layers_select_in_one_launch(heads, nb, small):
+    lib = B.load()
+    p = _p(heads, 1, 64 * nb)
+    t = B.head_table([(B.TOPK, 3)] * heads)
+    ws = lib.saf3r_select_workspace_bytes(ctypes.byref(p), t)
+    rows = lib.saf3r_stub_topk_rows_per_group
+    for workspace, expect in ((None, 4 if small else 16), (OK, 4 if small else 0)):
+        assert lib.saf3r_select_blocks(ctypes.byref(p), t, OK, OK, OK, OK, 3, None, workspace,
+                                       ws if workspace else 0, None) == 0
+        assert rows() == expect
+
+
 # rows that four waves share in bf16: beside short lists, in key ranges (with the workspace), strided, odd block counts
 @pytest.mark.parametrize("heads,frames,T,table", [
     (4, 1, 520, [(B.DENSE, 0), (B.TOPK, 8), (B.TOPK, 1), (B.STRIDE, 1)]),

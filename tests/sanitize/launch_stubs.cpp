@@ -31,6 +31,7 @@ bool blocks_ok(int64_t n, int nb) { return n >= 1 && nb == (int)((n + kBlock - 1
 hipError_t launch_status(bool ok) { return ok ? hipSuccess : hipErrorInvalidValue; }
 
 int attention_launches[2] = {0, 0};  // of one wave and of four waves to a workgroup
+int topk_rows_per_group = 0;         // of the last Top-K launch; 0 for the pair with a workspace
 
 // The workgroups of a list or strided launch take every (head, key range,
 // query block) exactly once: one wave each, or all four waves of a workgroup
@@ -71,6 +72,7 @@ bool covers_every_item(const AttnArgs& a) {
 
 }  // namespace
 
+extern "C" int saf3r_stub_topk_rows_per_group() { return topk_rows_per_group; }
 extern "C" int saf3r_stub_attention_launches(int waves) { return attention_launches[waves == 4 ? 1 : 0]; }
 
 hipError_t launch_pool(int dtype, const void* q, const void* k, double* qp, double* kp,
@@ -85,6 +87,7 @@ hipError_t launch_select_topk(const double* qp, const double* kpT, int32_t* idx,
   ok = ok && (a.rows_per_group == 1 || a.rows_per_group == 2 || a.rows_per_group == 4 ||
               a.rows_per_group == 8 || a.rows_per_group == 16);
   ok = ok && lds_bytes == topk_lds_bytes(a.rows_per_group, a.nb) && lds_bytes <= 160 * 1024;
+  topk_rows_per_group = a.rows_per_group;
   for (int i = 0; ok && i < a.n_heads; ++i) ok = a.topk[i] >= 1 && a.topk[i] <= a.nb && a.topk[i] <= a.cap;
   return launch_status(ok);
 }
@@ -93,6 +96,7 @@ hipError_t launch_select_topk_ws(const double* qp, const double* kpT, uint32_t* 
                                  int32_t* cnt, double*, const TopKArgs& a, hipStream_t) {
   bool ok = qp && kpT && keys && idx && cnt && blocks_ok(a.n, a.nb) &&
             heads_ok(a.head, a.n_heads, kMaxHeads) && a.n_heads >= 1;
+  topk_rows_per_group = 0;
   for (int i = 0; ok && i < a.n_heads; ++i) ok = a.topk[i] >= 1 && a.topk[i] <= a.nb && a.topk[i] <= a.cap;
   return launch_status(ok);
 }

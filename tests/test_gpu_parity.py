@@ -866,6 +866,33 @@ def test_lists_of_heads_selected_together(gpu_lib, n):
     assert (res["cnt"][8] == nb).all() and (res["idx"][8][:, :nb] == np.arange(nb)).all()
 
 
+@pytest.mark.parametrize("heads", [8, 9])  # 512 and 576 groups of four rows
+def test_lists_either_side_of_the_one_launch_line(gpu_lib, heads):
+    import torch
+
+    import paper_2607_03612_amd as P
+
+    nb = 256
+    table = [(O.TOPK, 1 + 29 * h) for h in range(heads)] + [(O.FRAME_LOCAL, 0)]
+    w = Workload(f"line-{heads}", 4, nb * 16, "bf16", ("fixed", 1, 1, 50), heads=heads + 1)
+    q, k, _ = make_qkv(w, seed=4)
+    qp, kp = P.estimate_blocks(PT.to_device(q, "bf16"), PT.to_device(k, "bf16"), table, 4, nb * 16)
+    full = P.select_workspace_bytes(table, 4, nb * 16)
+    res = []
+    for nbytes in (0, full // heads * 3, full):
+        ws = torch.empty(nbytes // 4, dtype=torch.int32, device="cuda") if nbytes else None
+        idx, cnt, _ = P.select_blocks(qp, kp, table, 4, nb * 16, workspace=ws)
+        res.append({"idx": idx.cpu().numpy(), "cnt": cnt.cpu().numpy()})
+        assert np.array_equal(res[-1]["idx"], res[0]["idx"]) and np.array_equal(res[-1]["cnt"], res[0]["cnt"])
+    qn, kn = qp.cpu().numpy(), kp.cpu().numpy()
+    for h, (_, kk) in enumerate(table[:heads]):
+        scores = qn[h] @ kn[h] / 8
+        for i in range(0, nb, 17):
+            lst, margin = O.topk_row(scores[i], kk)
+            PT.check_lists(res[0], h, i, O.TOPK, lst, margin, nb, res[0]["idx"].shape[2],
+                           rank=PT.ranking(O.TOPK, kk, scores[i]))
+
+
 def test_equal_scores_keep_the_lowest_block_indices(gpu_lib):
     """Every key token equal: all block scores are the same float64 value, so
     the Top-K and global-probe selections reduce to the tie rule of the
