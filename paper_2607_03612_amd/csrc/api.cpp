@@ -5,8 +5,8 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 #include <limits>
-#include <numeric>
 #include <vector>
 
 #include "../../include/saf3r.h"
@@ -363,32 +363,83 @@ static bool splits_now(const Shape& s, const saf3r_head_cfg* table, int h, int c
          (int64_t)cost * (saf3r::kWaveSlots / 4) > 2 * work;
 }
 
+// The work items of one length in a launch: key blocks walked, mean and most.
+struct RowClass {
+  int cost, longest;
+  int64_t rows;
+};
+
+// About the time of a bf16 launch, in key blocks walked by a wave that has its
+// SIMD to itself, when the rows of the first `shared` classes (longest rows
+// first) are each shared by a workgroup's four waves and the others have a
+// wave each. The items are dealt out longest first over the chip, a shared one
+// per CU and turn, another one per SIMD. Down to each length the work so far
+// takes whole items of it, the last of them perhaps its class's longest; and
+// two items on a SIMD share its rate, so in a launch of more than one turn an
+// item takes up to twice as long, by what follows the first turn (lone waves:
+// of what follows kFirstTurn of one, as they are not dealt out evenly).
+static double launch_time(const std::vector<RowClass>& c, size_t shared) {
+  struct Dealt {
+    double length, longest, turns;
+  };
+  std::vector<Dealt> items;
+  double beyond = 0, room = shared ? 1 : saf3r::kFirstTurn, turns = 0;
+  for (size_t x = 0, y = shared; x < shared || y < c.size();) {
+    const double of_x = x < shared ? c[x].cost / 4.0 + saf3r::kSharedOverhead : 0;
+    const double of_y = y < c.size() ? c[y].cost + saf3r::kItemOverhead : 0;
+    const double length = std::max(of_x, of_y);
+    const bool is_shared = of_x >= of_y;
+    const RowClass& r = is_shared ? c[x++] : c[y++];
+    const double n = (double)r.rows / (is_shared ? saf3r::kCus : 4 * saf3r::kCus);
+    items.push_back({length, length + (r.longest - r.cost) / (is_shared ? 4.0 : 1.0), n});
+    beyond += (n - std::min(n, room)) * length;
+    room -= std::min(n, room);
+    turns += n;
+  }
+  if (turns <= 1) beyond = 0;
+  double work = 0, time = 0;
+  for (const Dealt& i : items) {
+    work += i.length * i.turns;
+    time = std::max({time, i.length * std::ceil(work / i.length - 1e-6) + i.longest - i.length,
+                     i.longest + std::min(i.longest, beyond)});
+  }
+  return time;
+}
+
 // The heads of a bf16 launch whose rows the four waves of a workgroup share,
-// as a least cost of a row (key blocks walked); INT_MAX for none. cost[p] is a
-// head's mean row, rows[p] its work items. A launch takes about the larger of
-// its longest item and its work per wave slot, each item kItemOverhead more
-// than it walks; sharing cuts an item to a quarter and makes four of it. Of
-// the heads from the longest rows down, as many share as make that least.
-static int shared_rows_cost(const std::vector<int>& cost, const std::vector<int64_t>& rows) {
+// as a least cost of a row; INT_MAX for none. A launch takes at least the
+// longer of its longest row and its work per wave slot; sharing cuts an item to
+// a quarter and makes four of it, each with its own start and end. Of the
+// classes from the longest rows down, as many share as make that least, as long
+// as the launch dealt out in turns gets shorter, too.
+static int shared_rows_cost(std::vector<RowClass> c) {
   constexpr int kO = saf3r::kItemOverhead;
-  std::vector<int> by(cost.size());
-  std::iota(by.begin(), by.end(), 0);
-  std::sort(by.begin(), by.end(), [&](int x, int y) { return cost[x] > cost[y]; });
+  std::sort(c.begin(), c.end(), [](const RowClass& x, const RowClass& y) { return x.cost > y.cost; });
+  size_t n = 0;
   double total = 0;
-  for (size_t p = 0; p < by.size(); ++p) total += (double)rows[p] * (cost[p] + kO);
-  auto time = [&](double longest) { return std::max(longest, total / saf3r::kWaveSlots); };
-  double best = by.empty() ? 0 : time(cost[by[0]] + kO);
-  int least = std::numeric_limits<int>::max();
-  for (size_t p = 0; p < by.size(); ++p) {
-    if (cost[by[p]] < saf3r::kShareMinBlocks) break;
-    total += (double)rows[by[p]] * 3 * kO;
-    const int next = p + 1 < by.size() ? cost[by[p + 1]] : 0;
-    if (next == cost[by[p]]) continue;  // equal rows are treated alike
-    const double t = time(std::max(cost[by[0]] / 4.0 + kO, next > 0 ? (double)(next + kO) : 0.0));
-    if (t < 0.95 * best) {
-      best = t;
-      least = cost[by[p]];
+  for (const RowClass r : c) {
+    total += (double)r.rows * (r.cost + kO);
+    if (n > 0 && c[n - 1].cost == r.cost) {
+      c[n - 1].longest = std::max(c[n - 1].longest, r.longest);
+      c[n - 1].rows += r.rows;
+    } else {
+      c[n++] = r;
     }
+  }
+  c.resize(n);
+  int least = std::numeric_limits<int>::max();
+  if (n == 0) return least;
+  auto bound = [&](double longest) { return std::max(longest, total / saf3r::kWaveSlots); };
+  double best = bound(c[0].cost + kO), in_turns = 0;
+  for (size_t p = 0; p < n && c[p].cost >= saf3r::kShareMinBlocks; ++p) {
+    total += (double)c[p].rows * 3 * kO;
+    const double next = p + 1 < n ? c[p + 1].cost + kO : 0;
+    const double t = bound(std::max(c[0].cost / 4.0 + kO, next));
+    if (t >= saf3r::kShareGain * best) continue;
+    if (in_turns == 0) in_turns = launch_time(c, 0);
+    if (launch_time(c, p + 1) >= in_turns) continue;
+    best = t;
+    least = c[p].cost;
   }
   return least;
 }
@@ -480,16 +531,15 @@ saf3r_status saf3r_sparse_attention(const saf3r_problem* problem, const saf3r_he
   auto order = [&](std::vector<int>& heads) -> bool {
     bool any = false;
     if (bf16) {
-      std::vector<int> cost;
-      std::vector<int64_t> rows;
+      std::vector<RowClass> rows;
       for (int h : heads) {
         const int mean = attention_cost(s, table, h, fl.mean);
-        cost.push_back(is_split[h] ? (mean + saf3r::kSplitChunks - 1) / saf3r::kSplitChunks : mean);
-        rows.push_back((int64_t)s.nb * (is_split[h] ? saf3r::kSplitChunks : 1));
+        const int ranges = is_split[h] ? saf3r::kSplitChunks : 1;
+        rows.push_back({(mean + ranges - 1) / ranges, item_cost[h], (int64_t)s.nb * ranges});
       }
-      const int least = shared_rows_cost(cost, rows);
+      const int least = shared_rows_cost(rows);
       for (size_t p = 0; p < heads.size(); ++p) {
-        if (cost[p] < least) continue;
+        if (rows[p].cost < least) continue;
         is_shared[heads[p]] = 1;
         item_cost[heads[p]] = (item_cost[heads[p]] + 3) / 4;
         any = true;

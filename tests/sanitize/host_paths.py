@@ -82,7 +82,7 @@ def test_small_layers_select_in_one_launch(heads, nb, small):
 @pytest.mark.parametrize("heads,frames,T,table", [
     (4, 1, 520, [(B.DENSE, 0), (B.TOPK, 8), (B.TOPK, 1), (B.STRIDE, 1)]),
     (5, 2, 1000, [(B.DENSE, 0), (B.TOPK, 31), (B.FRAME_LOCAL, 0), (B.ANCHOR, 1), (B.TOPK, 3)]),
-    (1, 1, 8300, [(B.DENSE, 0)]),
+    (1, 1, 8190, [(B.DENSE, 0)]),
     (16, 8, 1374, [(B.FRAME_LOCAL, 0)] * 6 + [(B.DENSE, 0)] + [(B.TOPK, 13)] * 9),
     (3, 4, 1374, [(B.STRIDE, 3), (B.STRIDE, 500), (B.STRIDE, 11)]),
     (12, 20, 1001, [(B.DENSE, 0)] * 3 + [(B.FRAME_LOCAL, 0)] * 4 + [(B.TOPK, 32)] * 5),
@@ -99,6 +99,21 @@ def test_shared_rows_reach_consistent_launches(heads, frames, T, table, workspac
     assert lib.saf3r_sparse_attention(ctypes.byref(p), t, OK, OK, OK, OK, OK, cap, OK, OK,
                                       OK if workspace else None, max(aws, 16) if workspace else 0, None) == 0
     assert launches(4) > before
+
+
+# equal rows: shared while that takes fewer turns of the chip (one workgroup per CU), not beyond
+@pytest.mark.parametrize("heads,nb,k,waves", [
+    (1, 130, 8, 4), (1, 653, 8, 1), (8, 86, 8, 1), (1, 512, 16, 4), (1, 520, 16, 1), (1, 800, 16, 1), (1, 653, 48, 4),
+    (4, 203, 12, 1), (8, 640, 128, 1), (1, 130, 7, 1),
+])
+def test_equal_rows_are_shared_where_that_takes_fewer_turns(heads, nb, k, waves):
+    lib = B.load()
+    p = _p(heads, 1, 64 * nb)
+    t = B.head_table([(B.TOPK, k)] * heads)
+    launches = lib.saf3r_stub_attention_launches
+    before = [launches(1), launches(4)]
+    assert lib.saf3r_sparse_attention(ctypes.byref(p), t, OK, OK, OK, OK, OK, k, OK, None, None, 0, None) == 0
+    assert [launches(1) - before[0], launches(4) - before[1]] == [int(waves == 1), int(waves == 4)]
 
 
 def test_all_dense_table_is_one_launch():

@@ -624,11 +624,13 @@ def test_fp32_infinities_and_nans_stay_where_they_belong(gpu_lib, tensor, value)
 
 
 # rows of 8, 9, 31 and 33 blocks beside rows too short to share; dense rows beside short lists; every head dense; one
-# block (nothing to share); the workspace's key ranges over shared rows (a single dense head of 130 blocks)
+# block (nothing to share); the workspace's key ranges over shared rows (a single dense head of 128 blocks) and over
+# rows of their own (130 blocks)
 @pytest.mark.parametrize("frames,T,table", [
     (1, 520, [(O.DENSE, 0), (O.TOPK, 8), (O.TOPK, 1), (O.STRIDE, 1)]),
     (2, 1000, [(O.DENSE, 0), (O.TOPK, 31), (O.FRAME_LOCAL, 0), (O.ANCHOR, 1), (O.TOPK, 3)]),
     (3, 704, [(O.DENSE, 0)] * 3), (1, 64, [(O.DENSE, 0)] * 2), (1, 8300, [(O.DENSE, 0)]),
+    (1, 8190, [(O.DENSE, 0)]),
     (4, 1374, [(O.STRIDE, 3), (O.STRIDE, 500), (O.STRIDE, 11)]),
 ])
 @pytest.mark.parametrize("workspace", [False, True])
