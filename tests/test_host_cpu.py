@@ -1,6 +1,8 @@
 """Host-side logic of the profiler (no GPU): the baseline stride, the FLOP
 count of Eq. 2 and the progressive-substitution choice, each against the
 oracle's own definition on many seeded cases."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -123,3 +125,16 @@ def test_capacity_and_attention_split_match_oracle_lists(frames, T):
             n_split = sum(1 for x in lens if splits(x, True)) + n_dense * splits(nb, False)
             want = 4 * nb * 16896 * n_split
             assert lib.saf3r_attention_workspace_bytes(ctypes.byref(p), t) == want, (table, lens)
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 5, 31, 63, 64, 65, 100, 127, 128, 129, 192, 261, 1374])
+def test_frame_local_capacity_at_every_frame_size(T):
+    """Frames below a block, of whole blocks and across blocks: the capacity of
+    a frame-local table is the longest of the oracle's rows."""
+    lib = B.load()
+    for frames in (1, 2, 3, 7, 40):
+        n = frames * T
+        p = B.problem(2, frames, T, B.BF16)
+        want = max(len(O.frame_local_row(i, n, T, 64)) for i in range(-(-n // 64)))
+        t = B.head_table([(B.FRAME_LOCAL, 0), (B.DENSE, 0)])
+        assert lib.saf3r_index_capacity(ctypes.byref(p), t) == want, (T, frames)
