@@ -268,8 +268,8 @@ saf3r_status saf3r_select_blocks(const saf3r_problem* problem, const saf3r_head_
     return SAF3R_ERR_UNSUPPORTED;
   }
 
-  // Beside Top-K heads the static lists, and on small layers the global-probe
-  // ones, are written by the Top-K heads' first launch.
+  // Beside Top-K heads the static lists, and on small layers with not too long
+  // rows the global-probe ones, are written by the Top-K heads' first launch.
   auto beside = [&](int16_t head, int32_t param, int8_t pattern) {
     const int at = ta.n_heads + ta.n_static + ta.n_global;
     ta.head[at] = head;
@@ -280,7 +280,8 @@ saf3r_status saf3r_select_blocks(const saf3r_problem* problem, const saf3r_head_
     for (; ta.n_static < sa.n_heads; ++ta.n_static)
       beside(sa.head[ta.n_static], sa.param[ta.n_static], sa.pattern[ta.n_static]);
     sa.n_heads = 0;
-    if (s.nb <= saf3r::kGlobalFusedBlocks) {
+    const int64_t entries = (int64_t)s.nb * cap / (workspace_or_null && !one_launch ? 1 : 2);
+    if (s.nb <= saf3r::kGlobalFusedBlocks && entries <= saf3r::kGlobalFusedEntries) {
       for (; ta.n_global < ga.n_heads; ++ta.n_global) beside(ga.head[ta.n_global], ga.topk[ta.n_global], 0);
       ga.n_heads = 0;
     }

@@ -54,11 +54,15 @@ struct TopKArgs {
 };
 // Global-probe heads of layers up to this size go with the Top-K launch: their
 // one workgroup per head takes 6 KB + 12 bytes per block of LDS and writes
-// every row itself. us for 4 Top-K heads and two such, with the Top-K launch /
-// in launches of their own: 9.7 / 23.1 at 128 blocks, 44.8 / 48.9 at 651, 61 / 67
-// at 900, 71 / 66 at 1024, 151 / 136 at 1700; beside 10 Top-K heads 85 / 105 at
-// 1024; without a workspace 52 / 55 at 1024.
+// every row itself, so only up to so many list entries of a head (nb * cap; in
+// one launch without a workspace, where the rows beside them take longer, twice
+// as many). us for 4 Top-K heads and two such, with the Top-K launch / in
+// launches of their own: 10 / 23 at 128 blocks, 51 / 55 at 651 and 53 k entries,
+// 50 / 51 at 105 k, 61 / 53 at 211 k, 69 / 65 at 1024 and 131 k, 155 / 75 at
+// 1049 k; beside 10 Top-K heads 86 / 107 at 1024 and 131 k; without a workspace
+// 46 / 50 at 651 and 211 k, 55 / 59 at 1024 and 262 k, 60 / 53 at 800 and 320 k.
 constexpr int kGlobalFusedBlocks = 1024;
+constexpr int64_t kGlobalFusedEntries = 1 << 17;
 // Top-K rows of layers up to kOneLaunchBlocks are scored and selected in one
 // launch with or without a workspace, four rows to a workgroup, as long as that
 // makes at most two workgroups per CU: a third one's turn costs more than the

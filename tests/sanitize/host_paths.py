@@ -101,6 +101,20 @@ def test_shared_rows_reach_consistent_launches(heads, frames, T, table, workspac
     assert launches(4) > before
 
 
+# a global-probe head's one workgroup writes nb * cap entries: beside the Top-K launch up to 2^17 of them, twice that in one launch
+@pytest.mark.parametrize("nb,cap,with_ws,without", [(512, 256, 1, 1), (512, 257, 0, 1), (512, 512, 0, 1), (1024, 128, 1, 1),
+                                                    (1024, 256, 0, 1), (1024, 257, 0, 0), (1025, 4, 0, 0), (256, 512, 1, 1)])
+def test_global_probe_lists_beside_the_topk_launch(nb, cap, with_ws, without):
+    lib = B.load()
+    t = B.head_table([(B.TOPK, 3), (B.GLOBAL_PROBE, 4)])
+    p = _p(2, 1, 64 * nb)
+    ws = lib.saf3r_select_workspace_bytes(ctypes.byref(p), t)
+    for workspace, fused in ((OK, with_ws), (None, without)):
+        assert lib.saf3r_select_blocks(ctypes.byref(p), t, OK, OK, OK, OK, cap, None, workspace,
+                                       ws if workspace else 0, None) == 0
+        assert lib.saf3r_stub_topk_global() == fused
+
+
 # equal rows: shared while that takes fewer turns of the chip (one workgroup per CU), not beyond
 @pytest.mark.parametrize("heads,nb,k,waves", [
     (1, 130, 8, 4), (1, 653, 8, 1), (8, 86, 8, 1), (1, 512, 16, 4), (1, 520, 16, 1), (1, 800, 16, 1), (1, 653, 48, 4),

@@ -26,12 +26,29 @@ bool heads_ok(const int16_t* head, int n, int limit) {
   return true;
 }
 
+// The Top-K heads and, after them, the static and the global-probe heads whose
+// lists the same launch writes.
+bool topk_heads_ok(const TopKArgs& a) {
+  if (a.n_heads < 0 || a.n_static < 0 || a.n_global < 0) return false;
+  if (a.n_global > 0 && a.nb > kGlobalFusedBlocks) return false;
+  if (a.n_static > 0 && a.tokens_per_frame < 1) return false;
+  if (!heads_ok(a.head, a.n_heads + a.n_static + a.n_global, kMaxHeads)) return false;
+  for (int i = 0; i < a.n_heads + a.n_static + a.n_global; ++i) {
+    const bool is_static = i >= a.n_heads && i < a.n_heads + a.n_static;
+    if (is_static ? a.pattern[i] != kDense && a.pattern[i] != kFrameLocal && a.pattern[i] != kAnchor && a.pattern[i] != kStride
+                  : a.topk[i] < 1 || a.topk[i] > a.nb || a.topk[i] > a.cap)
+      return false;
+  }
+  return true;
+}
+
 bool blocks_ok(int64_t n, int nb) { return n >= 1 && nb == (int)((n + kBlock - 1) / kBlock); }
 
 hipError_t launch_status(bool ok) { return ok ? hipSuccess : hipErrorInvalidValue; }
 
 int attention_launches[2] = {0, 0};  // of one wave and of four waves to a workgroup
 int topk_rows_per_group = 0;         // of the last Top-K launch; 0 for the pair with a workspace
+int topk_global = 0;                 // global-probe heads beside it
 
 // The workgroups of a list or strided launch take every (head, key range,
 // query block) exactly once: one wave each, or all four waves of a workgroup
@@ -73,6 +90,7 @@ bool covers_every_item(const AttnArgs& a) {
 }  // namespace
 
 extern "C" int saf3r_stub_topk_rows_per_group() { return topk_rows_per_group; }
+extern "C" int saf3r_stub_topk_global() { return topk_global; }
 extern "C" int saf3r_stub_attention_launches(int waves) { return attention_launches[waves == 4 ? 1 : 0]; }
 
 hipError_t launch_pool(int dtype, const void* q, const void* k, double* qp, double* kp,
@@ -83,20 +101,21 @@ hipError_t launch_pool(int dtype, const void* q, const void* k, double* qp, doub
 
 hipError_t launch_select_topk(const double* qp, const double* kpT, int32_t* idx, int32_t* cnt,
                               double*, const TopKArgs& a, size_t lds_bytes, hipStream_t) {
-  bool ok = qp && kpT && idx && cnt && blocks_ok(a.n, a.nb) && heads_ok(a.head, a.n_heads, kMaxHeads);
+  bool ok = qp && kpT && idx && cnt && blocks_ok(a.n, a.nb) && topk_heads_ok(a);
   ok = ok && (a.rows_per_group == 1 || a.rows_per_group == 2 || a.rows_per_group == 4 ||
               a.rows_per_group == 8 || a.rows_per_group == 16);
   ok = ok && lds_bytes == topk_lds_bytes(a.rows_per_group, a.nb) && lds_bytes <= 160 * 1024;
   topk_rows_per_group = a.rows_per_group;
+  topk_global = a.n_global;
   for (int i = 0; ok && i < a.n_heads; ++i) ok = a.topk[i] >= 1 && a.topk[i] <= a.nb && a.topk[i] <= a.cap;
   return launch_status(ok);
 }
 
 hipError_t launch_select_topk_ws(const double* qp, const double* kpT, uint32_t* keys, int32_t* idx,
                                  int32_t* cnt, double*, const TopKArgs& a, hipStream_t) {
-  bool ok = qp && kpT && keys && idx && cnt && blocks_ok(a.n, a.nb) &&
-            heads_ok(a.head, a.n_heads, kMaxHeads) && a.n_heads >= 1;
+  bool ok = qp && kpT && keys && idx && cnt && blocks_ok(a.n, a.nb) && topk_heads_ok(a) && a.n_heads >= 1;
   topk_rows_per_group = 0;
+  topk_global = a.n_global;
   for (int i = 0; ok && i < a.n_heads; ++i) ok = a.topk[i] >= 1 && a.topk[i] <= a.nb && a.topk[i] <= a.cap;
   return launch_status(ok);
 }

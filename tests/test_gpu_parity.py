@@ -868,6 +868,38 @@ def test_lists_of_heads_selected_together(gpu_lib, n):
     assert (res["cnt"][8] == nb).all() and (res["idx"][8][:, :nb] == np.arange(nb)).all()
 
 
+@pytest.mark.parametrize("nb,cap", [(512, 256), (512, 257), (1024, 128), (1024, 256), (1024, 257)])
+def test_global_probe_lists_either_side_of_the_fused_line(gpu_lib, nb, cap):
+    """Global-probe heads beside the Top-K heads' launch and in launches of
+    their own (2^17 list entries a head, 2^18 without a workspace): the same
+    lists, padded to the capacity, against the oracle."""
+    import torch
+
+    import paper_2607_03612_amd as P
+
+    T = nb * 64 - 11
+    table = [(O.TOPK, 100), (O.GLOBAL_PROBE, 128), (O.GLOBAL_PROBE, 1)]
+    w = Workload(f"fused-{nb}", 1, T, "bf16", ("fixed", 1, 1, 50), heads=3)
+    q, k, _ = make_qkv(w, seed=6)
+    qp, kp = P.estimate_blocks(PT.to_device(q, "bf16"), PT.to_device(k, "bf16"), table, 1, T)
+    res = []
+    for nbytes in (0, P.select_workspace_bytes(table, 1, T)):
+        ws = torch.empty(nbytes // 4, dtype=torch.int32, device="cuda") if nbytes else None
+        idx, cnt, _ = P.select_blocks(qp, kp, table, 1, T, cap=cap, workspace=ws)
+        res.append({"idx": idx.cpu().numpy(), "cnt": cnt.cpu().numpy()})
+    assert np.array_equal(res[1]["idx"], res[0]["idx"]) and np.array_equal(res[1]["cnt"], res[0]["cnt"])
+    qn, kn = qp.cpu().numpy(), kp.cpu().numpy()
+    size = np.full(nb, 64.0)
+    size[-1] = T - 64 * (nb - 1)
+    for h, (pattern, kk) in enumerate(table):
+        scores = qn[h] @ kn[h] / 8 if pattern == O.TOPK else np.tile((size @ qn[h] / T) @ kn[h] / 8, (nb, 1))
+        for i in range(0, nb, 73):
+            lst, margin = O.topk_row(scores[i], kk)
+            PT.check_lists(res[0], h, i, O.TOPK, lst, margin, nb, cap, rank=PT.ranking(O.TOPK, kk, scores[i]))
+        if pattern == O.GLOBAL_PROBE:
+            assert (res[0]["idx"][h] == res[0]["idx"][h][0]).all() and (res[0]["cnt"][h] == kk).all()
+
+
 @pytest.mark.parametrize("heads", [8, 9])  # 512 and 576 groups of four rows
 def test_lists_either_side_of_the_one_launch_line(gpu_lib, heads):
     import torch
