@@ -39,6 +39,9 @@ PEAK_F64_TFLOPS = 78.6      # MI355X fp64 (matrix and vector)
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "attn_traffic.json")
 
+# the Top-K selection: two launches, or one on small layers
+SELECT_KERNEL = "topk_score_kernel + topk_rows_kernel / select_topk_kernel"
+
 
 def log(*a):
     print(*a, file=sys.stderr, flush=True)
@@ -807,7 +810,7 @@ def main():
         "select_roofline": {
             # Top-K scores of every (query block, key block) pair in float64
             # on the matrix cores: 2 * nb^2 * 64 FLOP per Top-K head
-            "kernel": "topk_score_kernel + topk_rows_kernel", "bound": "mfma-fp64",
+            "kernel": SELECT_KERNEL, "bound": "mfma-fp64",
             "flop_per_launch": 2 * nb * nb * 64 * n_topk, "launch_ms": round(sel_ms, 4),
             "achieved": round(2 * nb * nb * 64 * n_topk / (sel_ms * 1e-3) / 1e12, 2),
             "peak": PEAK_F64_TFLOPS, "unit": "TFLOP/s",

@@ -116,9 +116,9 @@ constexpr int kSplitChunks = 4;
 // row (fp32: always; bf16: where that shortens the launch) and the merge
 // launch costs about 10 us: rows of kSplitMinWalk (bf16) or kSplitMinWalkF32
 // or more blocks whose quarter outlasts twice the layer's work per wave slot
-// (fp32, 16 heads, step time unsplit / split: 1044 tokens 54 / 64 us, 5496
-// tokens 128 / 165 us, 10992 tokens 357 / 369 us; a bf16 tile takes half the
-// time of an fp32 one).
+// (fp32 attention, unsplit / split: 16 heads, one or four of them dense, 1044
+// tokens 33 / 45 us, 5496 tokens 156 / 185, 10992 tokens 415 / 428; one dense
+// head of 5496 tokens 119 / 68, 8 heads of 10992 tokens with one 246 / 202).
 constexpr int kBalanceMinBlocks = 32;
 constexpr int kBalanceMinBlocksF32 = 8;
 constexpr int kSplitMinWalk = 128;
