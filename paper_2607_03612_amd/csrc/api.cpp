@@ -447,7 +447,7 @@ static int shared_rows_cost(std::vector<RowClass> c) {
     const double t = bound(std::max(c[0].cost / 4.0 + kO, next));
     if (t >= saf3r::kShareGain * best) continue;
     if (in_turns == 0) in_turns = launch_time(c, 0);
-    if (launch_time(c, p + 1) >= in_turns) continue;
+    if (launch_time(c, p + 1) >= saf3r::kShareGain * in_turns) continue;
     best = t;
     least = c[p].cost;
   }

@@ -126,8 +126,8 @@ constexpr int kSplitMinWalkF32 = 64;
 // Shared rows in bf16 (shared_rows_cost in api.cpp): the start and end of a
 // wave, and of one that shares a row, in key blocks' time, and the gain from
 // which rows are shared. On 2244 random tables (16 to 900 key blocks, 1 to 24
-// heads, no workspace) the launch so chosen takes 1.017 times the best of its
-// forms, always one wave a row 1.32 times; 23 tables are more than 4% slower than
+// heads, no workspace) the launch so chosen takes 1.018 times the best of its
+// forms, always one wave a row 1.32 times; 14 tables are more than 4% slower than
 // with one wave a row. (Without a look at whole turns 171, by up to half: 653
 // equal rows of 8 blocks take 20 us shared, 15 not; of 48 blocks 48 and 54; 130
 // rows of 8 blocks 8.6 and 12.)
