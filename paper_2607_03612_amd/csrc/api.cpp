@@ -280,8 +280,9 @@ saf3r_status saf3r_select_blocks(const saf3r_problem* problem, const saf3r_head_
     for (; ta.n_static < sa.n_heads; ++ta.n_static)
       beside(sa.head[ta.n_static], sa.param[ta.n_static], sa.pattern[ta.n_static]);
     sa.n_heads = 0;
-    const int64_t entries = (int64_t)s.nb * cap / (workspace_or_null && !one_launch ? 1 : 2);
-    if (s.nb <= saf3r::kGlobalFusedBlocks && entries <= saf3r::kGlobalFusedEntries) {
+    const int64_t turns = ((int64_t)batch * ((s.nb + 15) / 16) + saf3r::kCus - 1) / saf3r::kCus;
+    const int64_t entries = saf3r::kGlobalFusedEntries * turns * (workspace_or_null && !one_launch ? 1 : 2);
+    if (s.nb <= saf3r::kGlobalFusedBlocks && (int64_t)s.nb * cap <= entries) {
       for (; ta.n_global < ga.n_heads; ++ta.n_global) beside(ga.head[ta.n_global], ga.topk[ta.n_global], 0);
       ga.n_heads = 0;
     }

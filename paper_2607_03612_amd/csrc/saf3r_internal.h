@@ -54,13 +54,16 @@ struct TopKArgs {
 };
 // Global-probe heads of layers up to this size go with the Top-K launch: their
 // one workgroup per head takes 6 KB + 12 bytes per block of LDS and writes
-// every row itself, so only up to so many list entries of a head (nb * cap; in
-// one launch without a workspace, where the rows beside them take longer, twice
-// as many). us for 4 Top-K heads and two such, with the Top-K launch / in
-// launches of their own: 10 / 23 at 128 blocks, 51 / 55 at 651 and 53 k entries,
-// 50 / 51 at 105 k, 61 / 53 at 211 k, 69 / 65 at 1024 and 131 k, 155 / 75 at
-// 1049 k; beside 10 Top-K heads 86 / 107 at 1024 and 131 k; without a workspace
-// 46 / 50 at 651 and 211 k, 55 / 59 at 1024 and 262 k, 60 / 53 at 800 and 320 k.
+// every row itself, so only up to so many list entries of a head (nb * cap) for
+// each turn of the chip that the Top-K rows beside it take, twice as many in one
+// launch without a workspace, which takes longer. us for 4 Top-K heads and two
+// such, with the Top-K launch / in launches of their own: 10 / 23 at 128 blocks,
+// 51 / 55 at 651 and 53 k entries, 50 / 51 at 105 k, 61 / 53 at 211 k, 69 / 65 at
+// 1024 and 131 k, 155 / 75 at 1049 k; without a workspace 46 / 50 at 651 and 211
+// k, 55 / 59 at 1024 and 262 k, 60 / 53 at 800 and 320 k. Beside 10 Top-K heads
+// (three turns) 94 / 105 at 1024 and 262 k, 109 / 101 at 912 and 415 k; without a
+// workspace 80 / 110 at 1024 and 524 k, 127 / 122 at 1049 k.
+constexpr int kCus = 256;
 constexpr int kGlobalFusedBlocks = 1024;
 constexpr int64_t kGlobalFusedEntries = 1 << 17;
 // Top-K rows of layers up to kOneLaunchBlocks are scored and selected in one
@@ -136,7 +139,6 @@ constexpr int kSharedOverhead = 4;
 constexpr double kFirstTurn = 0.7;
 constexpr double kShareGain = 0.95;
 constexpr int kShareMinBlocks = 8;  // shorter rows are not worth four waves
-constexpr int kCus = 256;
 constexpr int64_t kWaveSlots = 2048;
 constexpr int64_t kSplitItemBytes = (int64_t)kBlock * kHeadDim * 4 + (int64_t)kBlock * 2 * 4;
 

@@ -101,18 +101,21 @@ def test_shared_rows_reach_consistent_launches(heads, frames, T, table, workspac
     assert launches(4) > before
 
 
-# a global-probe head's one workgroup writes nb * cap entries: beside the Top-K launch up to 2^17 of them, twice that in one launch
-@pytest.mark.parametrize("nb,cap,with_ws,without", [(512, 256, 1, 1), (512, 257, 0, 1), (512, 512, 0, 1), (1024, 128, 1, 1),
-                                                    (1024, 256, 0, 1), (1024, 257, 0, 0), (1025, 4, 0, 0), (256, 512, 1, 1)])
-def test_global_probe_lists_beside_the_topk_launch(nb, cap, with_ws, without):
+# a global-probe head's one workgroup writes nb * cap entries: beside the Top-K launch up to 2^17 of them for each turn of
+# 256 groups of 16 Top-K rows, twice that in one launch
+@pytest.mark.parametrize("topk,nb,cap,with_ws,without", [
+    (1, 512, 256, 1, 1), (1, 512, 257, 0, 1), (1, 512, 512, 0, 1), (1, 1024, 128, 1, 1), (1, 1024, 256, 0, 1),
+    (1, 1024, 257, 0, 0), (1, 1025, 4, 0, 0), (1, 256, 512, 1, 1), (4, 1024, 129, 0, 1), (5, 1024, 256, 1, 1),
+    (5, 1024, 257, 0, 1), (10, 1024, 384, 1, 1), (10, 1024, 768, 0, 1), (10, 1024, 769, 0, 0)])
+def test_global_probe_lists_beside_the_topk_launch(topk, nb, cap, with_ws, without):
     lib = B.load()
-    t = B.head_table([(B.TOPK, 3), (B.GLOBAL_PROBE, 4)])
-    p = _p(2, 1, 64 * nb)
+    t = B.head_table([(B.TOPK, 3)] * topk + [(B.GLOBAL_PROBE, 4)])
+    p = _p(topk + 1, 1, 64 * nb)
     ws = lib.saf3r_select_workspace_bytes(ctypes.byref(p), t)
     for workspace, fused in ((OK, with_ws), (None, without)):
         assert lib.saf3r_select_blocks(ctypes.byref(p), t, OK, OK, OK, OK, cap, None, workspace,
                                        ws if workspace else 0, None) == 0
-        assert lib.saf3r_stub_topk_global() == fused
+        assert lib.saf3r_stub_topk_global() == fused, workspace
 
 
 # equal rows: shared while that takes fewer turns of the chip (one workgroup per CU), not beyond
