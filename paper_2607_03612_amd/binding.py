@@ -145,18 +145,28 @@ def _stream(stream):
     return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
+def _torch_stream(stream):
+    import torch
+
+    return stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream)
+
+
 def _keep_until_done(stream, *temporaries):
     """Memory of tensors that end with the call: not handed out again before
     `stream`, where it is not the one they were allocated on, has run what the
     call enqueued."""
+    if stream is not None:
+        for t in temporaries:
+            t.record_stream(_torch_stream(stream))
+
+
+def _after_current(stream):
+    """`stream` waits for what the current one has been given, such as the
+    fill of a tensor that the call makes for itself."""
     import torch
 
-    if stream is None:
-        return
-    if not isinstance(stream, torch.cuda.Stream):
-        stream = torch.cuda.ExternalStream(stream.cuda_stream)
-    for t in temporaries:
-        t.record_stream(stream)
+    if stream is not None:
+        _torch_stream(stream).wait_stream(torch.cuda.current_stream())
 
 
 def _check(status: int, where: str):
@@ -198,10 +208,13 @@ def estimate_blocks(q, k, table, frames, tokens_per_frame, q_pooled=None, k_pool
     if frames * tokens_per_frame != N or len(table) != H:
         raise ValueError("frames * tokens_per_frame must equal N and len(table) the heads")
     nb = -(-N // BLOCK)
+    fill = q_pooled is None or k_pooled is None
     if q_pooled is None:
         q_pooled = torch.zeros((H, nb, HEAD_DIM), dtype=torch.float64, device=q.device)
     if k_pooled is None:
         k_pooled = torch.zeros((H, HEAD_DIM, nb), dtype=torch.float64, device=q.device)
+    if fill:
+        _after_current(stream)
     p = problem(H, frames, tokens_per_frame, _torch_dtype_code(q))
     _check(_lib().saf3r_estimate_blocks(ctypes.byref(p), head_table(table), _ptr(q), _ptr(k),
                                         _ptr(q_pooled), _ptr(k_pooled), _stream(stream)),
@@ -241,6 +254,8 @@ def select_blocks(q_pooled, k_pooled, table, frames, tokens_per_frame, cap=None,
     if block_cnt is None:
         block_cnt = torch.empty((H, nb), dtype=torch.int32, device=dev)
     scores = torch.zeros((H, nb, nb), dtype=torch.float64, device=dev) if want_scores else None
+    if want_scores:
+        _after_current(stream)
     p = problem(H, frames, tokens_per_frame, dtype)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(_lib().saf3r_select_blocks(ctypes.byref(p), head_table(table), _ptr(q_pooled),

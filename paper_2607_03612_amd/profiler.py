@@ -60,6 +60,10 @@ def profile_heads(calib, frames: int, tokens_per_frame: int, candidates, sigma: 
 
     if not calib:
         raise ValueError("at least one calibration input is needed")
+    if stream is not None:
+        # the copies of errors and lists to the host wait for the stream that is current
+        with torch.cuda.stream(B._torch_stream(stream)):
+            return profile_heads(calib, frames, tokens_per_frame, candidates, sigma, features)
     q0 = calib[0][0]
     H, N, _ = q0.shape
     configs = [(B.STRIDE, baseline_stride(sigma))] + [tuple(c) for c in candidates]
@@ -68,8 +72,7 @@ def profile_heads(calib, frames: int, tokens_per_frame: int, candidates, sigma: 
     costs = np.zeros((C, H))
     code = B._torch_dtype_code(q0)
     for n_in, (q, k, v) in enumerate(calib):
-        full, _ = B.sparse_attention(q, k, v, [(B.DENSE, 0)] * H, frames, tokens_per_frame,
-                                     stream=stream)
+        full, _ = B.sparse_attention(q, k, v, [(B.DENSE, 0)] * H, frames, tokens_per_frame)
         for c, (pattern, param) in enumerate(configs):
             table = [(pattern, param)] * H
             idx = cnt = None
@@ -80,15 +83,12 @@ def profile_heads(calib, frames: int, tokens_per_frame: int, candidates, sigma: 
                 nb = -(-N // B.BLOCK)
                 idx = torch.empty((H, nb, cap), dtype=torch.int32, device=q.device)
                 cnt = torch.empty((H, nb), dtype=torch.int32, device=q.device)
-                B.cosine_select(features[n_in], table, frames, tokens_per_frame, idx, cnt,
-                                stream=stream)
+                B.cosine_select(features[n_in], table, frames, tokens_per_frame, idx, cnt)
             elif pattern not in (B.DENSE, B.STRIDE):
-                qp, kp = B.estimate_blocks(q, k, table, frames, tokens_per_frame, stream=stream)
-                idx, cnt, _ = B.select_blocks(qp, kp, table, frames, tokens_per_frame, dtype=code,
-                                              stream=stream)
-            out, _ = B.sparse_attention(q, k, v, table, frames, tokens_per_frame, idx, cnt,
-                                        stream=stream)
-            errors[c] += B.nmse(full, out, frames, tokens_per_frame, stream=stream).cpu().numpy()
+                qp, kp = B.estimate_blocks(q, k, table, frames, tokens_per_frame)
+                idx, cnt, _ = B.select_blocks(qp, kp, table, frames, tokens_per_frame, dtype=code)
+            out, _ = B.sparse_attention(q, k, v, table, frames, tokens_per_frame, idx, cnt)
+            errors[c] += B.nmse(full, out, frames, tokens_per_frame).cpu().numpy()
             if idx is None:
                 costs[c] += attention_cost(pattern, param, N)
             else:

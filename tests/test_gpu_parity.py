@@ -1290,6 +1290,38 @@ def test_skip_heads_split_a_layer_across_streams(gpu_lib):
 # ------------------------------------------- bounds of the tile loads
 
 
+def test_calls_on_another_stream_wait_for_their_own_fills(gpu_lib):
+    """With the current stream still busy, a call on another one must not read
+    or write a tensor that it made before that stream has filled it; and the
+    profiler's results come from the stream that it ran on."""
+    import torch
+
+    import paper_2607_03612_amd as P
+    from paper_2607_03612_amd import profiler
+
+    q, k, v = (torch.randn((4, 3000, 64), device="cuda").to(torch.bfloat16) for _ in range(3))
+    table = [(P.TOPK, 9), (P.FRAME_LOCAL, 0), (P.TOPK, 5), (P.GLOBAL_PROBE, 7)]
+    candidates = [(P.FRAME_LOCAL, 0), (P.TOPK, 4)]
+    want = P.estimate_blocks(q, k, table, 3, 1000)
+    want_lists = P.select_blocks(*want, table, 3, 1000, want_scores=True)
+    want_profile = profiler.profile_heads([(q, k, v)], 3, 1000, candidates)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    torch.cuda._sleep(50_000_000)  # tens of milliseconds on the current stream
+    got = P.estimate_blocks(q, k, table, 3, 1000, stream=side)
+    torch.cuda._sleep(50_000_000)
+    lists = P.select_blocks(*got, table, 3, 1000, want_scores=True, stream=side)
+    torch.cuda.synchronize()
+    # rows of frame-local heads hold their list and -1; TOPK and probe rows all of theirs
+    for a, b in zip([*got, *lists], [*want, *want_lists]):
+        assert torch.equal(a, b)
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(50_000_000)
+    profile = profiler.profile_heads([(q, k, v)], 3, 1000, candidates, stream=side)
+    assert np.array_equal(profile["errors"], want_profile["errors"])
+    assert np.array_equal(profile["costs"], want_profile["costs"]) and profile["table"] == want_profile["table"]
+
+
 def test_temporaries_outlive_the_stream_that_reads_them(gpu_lib):
     """Calls on another stream, which is still busy when they return: what the
     current stream allocates and writes then must not be the memory of the
